@@ -49,7 +49,8 @@ constexpr int kMaxBlock = 4096;   // rows per sequence per block
 constexpr int kSkinnyRows = 64;   // blocks of at most this many rows (B*q) run the skinny GEMM kernels
 constexpr int kRecLoops = 64;     // generation loops enqueued between two host synchronisations, at most
 constexpr int kPreRoundRows = 1;  // blocks of more rows round normalised GEMM inputs once (rms_rows)
-constexpr int kQkvFloatRows = 8;  // except the QKV GEMM, which reads the float rows up to this many
+constexpr int kQkvFloatRows = 8;  // except the QKV GEMM, which reads the float rows up to this many, and
+constexpr int kFloatTiles = 256;  // any GEMM of at most this many column tiles (one round of workgroups)
 
 int make_dims(const sdsat_config* c, Dims* D, std::string* why) {
     if (!c) { *why = "config is NULL"; return SDSAT_EINVAL; }
@@ -182,11 +183,13 @@ void carve(sdsat_ctx* c, Carver& cv) {
     c->inv_freq = (double*)cv.take((size_t)(D.Dh / 2) * 8);
     c->rope = (float*)cv.take((size_t)D.S * (D.Dh / 2) * 8);
     c->x = (float*)cv.take((size_t)D.maxM * D.d * 4);
-    c->ssq = (float*)cv.take((size_t)D.maxM * D.n_ssq * 4);
-    c->xg = (float*)cv.take((size_t)D.maxM * D.d_pad * 4);
+    const size_t skinny = std::min(D.maxM, kSkinnyRows);   // large blocks keep neither
+    c->ssq = (float*)cv.take(skinny * D.n_ssq * 4);
+    c->xg = (float*)cv.take(skinny * D.d_pad * 4);
     c->qbuf = cv.take((size_t)D.maxB * D.maxQ * D.d * 4);
-    c->obuf = cv.take((size_t)D.maxM * D.d_pad * e);
-    c->ubuf = cv.take((size_t)D.maxM * D.F_pad * e);
+    const size_t m16 = align_up((size_t)D.maxM, 16);   // large blocks keep whole 16-row tiles
+    c->obuf = cv.take(m16 * D.d_pad * e);
+    c->ubuf = cv.take(m16 * D.F_pad * e);
     c->attn_part_floats = std::max<size_t>(1, attention_partial_floats(D.maxB, D.H, D.maxQ, D.Dh, D.S));
     c->attn_part = (float*)cv.take(c->attn_part_floats * 4);
     c->attn_ctr = (int*)cv.take(attention_counter_ints(D.maxB, D.H, D.maxQ) * 4);
@@ -218,7 +221,7 @@ void carve(sdsat_ctx* c, Carver& cv) {
     c->tree_rows = (int*)cv.take(bq * 4);
     c->tree_mask = (uint64_t*)cv.take(bq * 8);
     c->logits = (float*)cv.take(bq * D.V * 4);
-    c->hbuf = cv.take((size_t)D.maxM * D.d_pad * e);
+    c->hbuf = cv.take(m16 * D.d_pad * e);
     if (D.maxM > kSkinnyRows) c->c_y = (float*)cv.take((size_t)D.maxM * D.d * 4 * kPrefillMaxSplit);   // split-K parts
 }
 
@@ -305,14 +308,15 @@ int fits(sdsat_ctx* c, int B, int q, bool* ok) {
     return SDSAT_OK;
 }
 
+// out: float rows (out_f32), or elements in fragment order of out_rows rows (B*q, or that rounded up to 16)
 int attention_layer(sdsat_ctx* c, int layer, int B, int q, const uint64_t* mask, const float* qbuf, void* out,
-                    int out_f32, int ldo) {
+                    int out_f32, int ldo, int out_rows) {
     const Dims& D = c->D;
     if (!mask && q > kAttnSplitRows && attention_rows_supported(D.dtype, D.Dh)) {   // prefill: 64-row tiles
         AttnArgs a{};
         a.qbuf = qbuf; a.kc = layer_k(c, layer); a.vc = layer_v(c, layer); a.cache_len = c->cache_len;
         a.B = B; a.q = q; a.H = D.H; a.S_max = D.S; a.scale = (float)(1.0 / std::sqrt((double)D.Dh));
-        a.out = out; a.out_f32 = out_f32; a.ldo = ldo; a.err = c->err_flag;
+        a.out = out; a.out_f32 = out_f32; a.ldo = ldo; a.out_rows = out_rows; a.err = c->err_flag;
         hipEvent_t e0, e1;
         prof_pair(c, PK_ATTN, &e0, &e1);
         HIPCHK(c, launch_attention_rows(D.dtype, D.Dh, a, c->stream, e0, e1));
@@ -327,7 +331,7 @@ int attention_layer(sdsat_ctx* c, int layer, int B, int q, const uint64_t* mask,
     a.B = B; a.q = q; a.H = D.H; a.S_max = D.S;
     a.scale = (float)(1.0 / std::sqrt((double)D.Dh));
     a.splits = p.splits; a.cols = p.cols; a.part = c->attn_part; a.counter = c->attn_ctr;
-    a.out = out; a.out_f32 = out_f32; a.ldo = ldo; a.err = c->err_flag;
+    a.out = out; a.out_f32 = out_f32; a.ldo = ldo; a.out_rows = out_rows; a.err = c->err_flag;
     hipEvent_t e0, e1;
     prof_pair(c, PK_ATTN, &e0, &e1);
     HIPCHK(c, launch_attention(D.dtype, D.Dh, p, a, c->stream, e0, e1));
@@ -384,15 +388,15 @@ int large_block_impl(sdsat_ctx* c, int B, int q, const int32_t* tokens, float* l
     const float eps = c->cfg.rms_eps;
     hipEvent_t evb;
     prof_begin(c, logits ? PK_BLOCK : PK_PREFILL, &evb);
-    HIPCHK(c, launch_embed(D.dtype, c->embed, D.V + D.A, D.d, tokens, M, c->x, c->xg, c->attn_norm[0], D.d_pad,
-                           c->ssq, D.n_ssq, c->err_flag, c->stream));
+    const int M16 = (int)align_up((size_t)M, 16);   // rows of the activations' fragment order
     // layer 0's normalised input; later layers get theirs from the residual kernel before them
-    HIPCHK(c, launch_rms_rows(D.dtype, c->xg, D.d_pad, c->ssq, D.n_ssq, D.d, eps, M, c->hbuf, D.d_pad, c->stream));
+    HIPCHK(c, launch_embed_norm_rows(D.dtype, c->embed, D.V + D.A, tokens, M, D.d, c->x, c->attn_norm[0], eps, c->hbuf,
+                                     D.d_pad, c->err_flag, c->stream));
     for (int l = 0; l < D.L; ++l) {
         const void* const* w = c->w_src.data() + 1 + 9 * l;   // attn_norm, wq, wk, wv, wo, ffn_norm, wg, wu, wd
         int rc = big_gemm_qkv(c, B, q, c->hbuf, w, l);
         if (rc) return rc;
-        rc = attention_layer(c, l, B, q, nullptr, (const float*)c->qbuf, c->obuf, 0, D.d_pad);
+        rc = attention_layer(c, l, B, q, nullptr, (const float*)c->qbuf, c->obuf, 0, D.d_pad, M16);
         if (rc) return rc;
         const size_t y_part = (size_t)D.maxM * D.d;   // offset between split-K partials in c_y
         int parts = 1;
@@ -426,15 +430,17 @@ int forward_block_impl(sdsat_ctx* c, int B, int q, const int32_t* tokens, const 
     // Both give the same element-type values (same partial-sum order, same
     // rounding).  Measured on the 7B shape at 6 rows: the QKV GEMM's 768
     // workgroups re-reading float rows cost less than an rms_rows launch (block
-    // 3.154 -> 3.148 ms), gate/up's 1376 more (3.154 -> 3.194 ms); at 13B's 11
-    // rows QKV also loses (6.86 -> 7.14 ms).
-    auto norm_input = [&](GemmArgs& g, int float_rows) -> int {
+    // 3.154 -> 3.148 ms), gate/up's 1376 more (29.1 + 4.6 us -> 35.2 us a layer);
+    // at 13B's 11 rows QKV also loses (6.86 -> 7.14 ms).  A small model's GEMMs
+    // (one round of workgroups) save the launch: tiny decoder, 6 rows, gate/up
+    // 3.8 + 3.4 us -> 6.0 us, LM head 3.3 + 3.4 us -> 5.4 us.
+    auto norm_input = [&](GemmArgs& g, int float_rows, int n_tiles) -> int {
         g.ldx = D.d_pad;
-        if (M <= float_rows) {
+        if (M <= (n_tiles <= kFloatTiles ? kQkvFloatRows : float_rows)) {
             g.xf = c->xg; g.ssq = c->ssq; g.n_ssq = D.n_ssq; g.eps = c->cfg.rms_eps;
             return SDSAT_OK;
         }
-        HIPCHK(c, launch_rms_rows(D.dtype, c->xg, D.d_pad, c->ssq, D.n_ssq, D.d, c->cfg.rms_eps, M, c->hbuf, D.d_pad,
+        HIPCHK(c, launch_rms_rows(D.dtype, c->xg, D.d_pad, c->ssq, D.n_ssq, D.d, c->cfg.rms_eps, M, c->hbuf,
                                   c->stream));
         g.xa = c->hbuf;
         return SDSAT_OK;
@@ -447,14 +453,14 @@ int forward_block_impl(sdsat_ctx* c, int B, int q, const int32_t* tokens, const 
         // attention sub-block: RMSNorm -> QKV (+RoPE, KV write) -> attention -> O (+residual);
         // xg holds x o (the gain of the RMSNorm the next GEMM applies)
         GemmArgs a{};
-        int rc = norm_input(a, kQkvFloatRows);
+        int rc = norm_input(a, kQkvFloatRows, D.nt_qkv);
         if (rc) return rc;
         a.qbuf = c->qbuf; a.kc = layer_k(c, l); a.vc = layer_v(c, l);
         a.cache_len = c->cache_len; a.q = q; a.H = D.H; a.Dh = D.Dh; a.S_max = D.S; a.mask = mask;
         a.rope = c->rope;
         rc = run_gemm(c, PK_QKV, EP_QKV, M, D.nt_qkv, D.ks_d, 3 * D.d, D.d, c->w_qkv[l], a);
         if (rc) return rc;
-        rc = attention_layer(c, l, B, q, mask, (const float*)c->qbuf, c->obuf, 0, D.d_pad);
+        rc = attention_layer(c, l, B, q, mask, (const float*)c->qbuf, c->obuf, 0, D.d_pad, M);
         if (rc) return rc;
         GemmArgs o{};
         o.xa = c->obuf; o.ldx = D.d_pad; o.resid = c->x; o.ldy = D.d; o.xg_out = c->xg; o.ldxg = D.d_pad;
@@ -463,7 +469,7 @@ int forward_block_impl(sdsat_ctx* c, int B, int q, const int32_t* tokens, const 
         if (rc) return rc;
         // feed-forward sub-block: RMSNorm -> gate/up (+SwiGLU) -> down (+residual)
         GemmArgs f{};
-        rc = norm_input(f, kPreRoundRows);
+        rc = norm_input(f, kPreRoundRows, D.nt_gu);
         if (rc) return rc;
         f.uout = c->ubuf; f.F = D.F; f.ldu = D.F_pad;
         rc = run_gemm(c, PK_GATEUP, EP_SWIGLU, M, D.nt_gu, D.ks_d, 2 * D.F, D.d, c->w_gu[l], f);
@@ -476,7 +482,7 @@ int forward_block_impl(sdsat_ctx* c, int B, int q, const int32_t* tokens, const 
     }
     if (logits) {
         GemmArgs h{};
-        int rc = norm_input(h, kPreRoundRows);
+        int rc = norm_input(h, kPreRoundRows, D.nt_lm);
         if (rc) return rc;
         h.y = logits; h.ldy = D.V;
         rc = run_gemm(c, PK_LM, EP_STORE, M, D.nt_lm, D.ks_d, D.V, D.d, c->w_lm, h);
@@ -612,11 +618,13 @@ int sdsat_init(const sdsat_config* cfg, const void* const* weights, int32_t n_we
             c->err = "cache fill failed";
             return init_fail(SDSAT_EDEVICE);
         }
-        // activation pads must read as zero
-        (void)launch_fill_i32((int*)c->xg, (size_t)D.maxM * D.d_pad, 0, c->stream);
-        (void)launch_fill_i32((int*)c->obuf, (size_t)D.maxM * D.d_pad * D.esz / 4, 0, c->stream);
-        (void)launch_fill_i32((int*)c->ubuf, (size_t)D.maxM * D.F_pad * D.esz / 4, 0, c->stream);
-        (void)launch_fill_i32((int*)c->hbuf, (size_t)D.maxM * D.d_pad * D.esz / 4, 0, c->stream);
+        // activations start finite (their columns past d_model, of which heads of 64 or 128 columns leave
+        // none, and past d_ffn, which every SwiGLU epilogue writes, must read as zero)
+        const size_t m16 = align_up((size_t)D.maxM, 16);
+        (void)launch_fill_i32((int*)c->xg, (size_t)std::min(D.maxM, kSkinnyRows) * D.d_pad, 0, c->stream);
+        (void)launch_fill_i32((int*)c->obuf, m16 * D.d_pad * D.esz / 4, 0, c->stream);
+        (void)launch_fill_i32((int*)c->ubuf, m16 * D.F_pad * D.esz / 4, 0, c->stream);
+        (void)launch_fill_i32((int*)c->hbuf, m16 * D.d_pad * D.esz / 4, 0, c->stream);
         (void)launch_fill_i32(c->verify_cnt, D.maxB, 0, c->stream);
         (void)launch_fill_i32(c->attn_ctr, attention_counter_ints(D.maxB, D.H, D.maxQ), 0, c->stream);
         (void)launch_fill_i32(c->cache_len, D.maxB, 0, c->stream);
@@ -965,7 +973,7 @@ int sdsat_attention(sdsat_ctx* c, int32_t layer, int32_t batch, int32_t q, const
     if (rc) return rc;
     if (!ok) return fail(c, SDSAT_ECAPACITY, "cache_len + q exceeds max_ctx");
     HIPCHK(c, hipMemcpyAsync(c->qbuf, d_q, (size_t)batch * q * D.d * 4, hipMemcpyDeviceToDevice, c->stream));
-    return attention_layer(c, layer, batch, q, d_ancestor_mask, (const float*)c->qbuf, d_out, 1, D.d);
+    return attention_layer(c, layer, batch, q, d_ancestor_mask, (const float*)c->qbuf, d_out, 1, D.d, batch * q);
 }
 
 size_t sdsat_linear_packed_bytes(int32_t dtype, int32_t N, int32_t K) {

@@ -211,6 +211,24 @@ __device__ __forceinline__ void attend_block(const Frag<T> (&kf)[2][NDS], const 
     }
 }
 
+// Columns d .. d + 3 of head h (d a multiple of 4) of block row m: float rows,
+// or the O GEMM's input in fragment order (the four stay in one chunk).
+template <typename T, int DH>
+__device__ __forceinline__ void store_out(const AttnArgs& a, int b, int h, int m, int d, f32x4_t v) {
+    const int row = b * a.q + m, col = h * DH + d;
+    if (a.out_f32) {
+        float* po = reinterpret_cast<float*>(a.out) + (size_t)row * a.ldo + col;   // the caller's: float-aligned
+#pragma unroll
+        for (int r = 0; r < 4; ++r) po[r] = v[r];
+        return;
+    }
+    T* po = reinterpret_cast<T*>(a.out) + frag_off(row, col, a.ldo, a.out_rows);
+    if constexpr (sizeof(T) == 2)
+        *reinterpret_cast<uint2*>(po) = uint2{f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3])};
+    else
+        *reinterpret_cast<f32x4_t*>(po) = v;
+}
+
 // Merge the split partials of one (sequence, head, 16-row tile): each thread
 // takes 4 head dimensions of a row, log-sum-exp over the splits in split
 // order.  The partials are read with device-coherent (agent-scope) loads.
@@ -253,16 +271,7 @@ __device__ __forceinline__ void combine_tile(const AttnArgs& a, int bh, int rt, 
             }
         }
         const float inv = 1.0f / den;
-        const size_t row = ((size_t)b * a.q + m) * a.ldo + (size_t)h * DH + d;
-        if (a.out_f32) {
-            float* po = reinterpret_cast<float*>(a.out) + row;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) po[r] = acc[r] * inv;
-        } else {
-            T* po = reinterpret_cast<T*>(a.out) + row;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) po[r] = to_elem<T>(acc[r] * inv);
-        }
+        store_out<T, DH>(a, b, h, m, d, acc * inv);
     }
 }
 
@@ -450,19 +459,7 @@ __global__ void __launch_bounds__(512) attn_kernel(AttnArgs a) {
                 continue;
             }
             const float inv = 1.0f / den;
-            const size_t row = ((size_t)b * q + m) * a.ldo + (size_t)h * DH;
-            if (a.out_f32) {
-                float* po = reinterpret_cast<float*>(a.out) + row + d;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) po[r] = acc[r] * inv;
-            } else if constexpr (sizeof(T) == 2) {   // 4 bf16 in one 8-byte store
-                const uint2 pk = {f32x2_to_bf16x2(acc[0] * inv, acc[1] * inv), f32x2_to_bf16x2(acc[2] * inv, acc[3] * inv)};
-                *reinterpret_cast<uint2*>(reinterpret_cast<T*>(a.out) + row + d) = pk;
-            } else {
-                T* po = reinterpret_cast<T*>(a.out) + row + d;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) po[r] = to_elem<T>(acc[r] * inv);
-            }
+            store_out<T, DH>(a, b, h, m, d, acc * inv);
         }
     }
     if (a.splits > 1) {
@@ -628,24 +625,9 @@ __global__ void __launch_bounds__(64 * kRowWaves) attn_rows_kernel(AttnArgs a) {
     const float gmax = fmaxf(rmax, m1);
     const float a0 = rmax == -INFINITY ? 0.f : expf(rmax - gmax), a1 = m1 == -INFINITY ? 0.f : expf(m1 - gmax);
     const float inv = 1.0f / (a0 * rsum + a1 * s1);
-    const size_t row = ((size_t)b * q + m) * a.ldo + (size_t)h * DH;
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) {
-        const int d = 16 * dt + 4 * g;
-        const f32x4_t acc = o[dt] * a0 + m_o[dt * 64 + lane] * a1;
-        if (a.out_f32) {
-            float* po = reinterpret_cast<float*>(a.out) + row + d;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) po[r] = acc[r] * inv;
-        } else if constexpr (E == 2) {   // 4 bf16 in one 8-byte store
-            const uint2 pk = {f32x2_to_bf16x2(acc[0] * inv, acc[1] * inv), f32x2_to_bf16x2(acc[2] * inv, acc[3] * inv)};
-            *reinterpret_cast<uint2*>(reinterpret_cast<T*>(a.out) + row + d) = pk;
-        } else {
-            T* po = reinterpret_cast<T*>(a.out) + row + d;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) po[r] = to_elem<T>(acc[r] * inv);
-        }
-    }
+    for (int dt = 0; dt < NDT; ++dt)
+        store_out<T, DH>(a, b, h, m, 16 * dt + 4 * g, (o[dt] * a0 + m_o[dt * 64 + lane] * a1) * inv);
 }
 
 hipError_t launch_attention_rows(int dtype, int head_dim, const AttnArgs& a, hipStream_t s, hipEvent_t ev0,

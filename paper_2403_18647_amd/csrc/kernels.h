@@ -39,10 +39,10 @@ size_t packed_elems(int n_tiles, int k_steps);
 
 // ---------------------------------------------------------------- skinny GEMM
 // One workgroup per 16-column tile (or 4 tiles for prefill chunks); its waves
-// split the contraction and reduce through LDS.  X rows are read straight from
-// global memory as matrix-core fragments, either
-//  * stored in the matrix element type with a row stride that covers the
-//    32-padded contraction length, zero past K (xa), or
+// split the contraction and reduce through LDS.  X is stored in fragment order
+// (device.h, frag_off: M rows of ldx columns, the 32-padded contraction length)
+// and read straight from global memory as matrix-core fragments, either
+//  * stored in the matrix element type, zero past K (xa), or
 //  * as the float rows x o g of an RMSNorm input (xf, gain already applied):
 //    each element is scaled by its row's 1/sqrt(mean(x^2) + eps) and rounded
 //    to the element type at the matrix-core input, the value a bf16 model
@@ -53,22 +53,22 @@ struct GemmArgs {
     int M, N, K;             // rows of X; real output columns; real contraction length
     int n_tiles, k_steps;    // packed tile counts
     const void* W;           // packed weights
-    const void* xa;          // T [M][ldx], or null when xf is given
-    const float* xf;         // float [M][ldx]: x o gain of the RMSNorm this GEMM consumes
+    const void* xa;          // T, or null when xf is given
+    const float* xf;         // float: x o gain of the RMSNorm this GEMM consumes
     int ldx;
     // RMSNorm row scales: 1/sqrt(sum_t ssq[m][t] / K + eps) (with xf)
     const float* ssq; int n_ssq; float eps;
     // epilogues
     float* y; int ldy;                   // EP_STORE: float [M][ldy]
     float* resid;                        // EP_RESID: float [M][ldy] (+=)
-    float* xg_out; int ldxg;             // EP_RESID: updated rows times gnext (the next RMSNorm's gain)
+    float* xg_out; int ldxg;             // EP_RESID: updated rows times gnext (the next RMSNorm's gain), fragment order
     const float* gnext;
     float* ssq_out;                      // EP_RESID: per-tile sums of squares [M][n_tiles]
     void* qbuf; void* kc; void* vc;      // EP_QKV: Q float [M][H][Dh]; layer base of K and V caches
     const int* cache_len; int q, H, Dh, S_max;
     const uint64_t* mask;                // [M] ancestor masks or null (chain)
     const float* rope;                   // [S_max][Dh/2][2] rotary cos, sin of position x base^(-2i/Dh)
-    void* uout; int F; int ldu;          // EP_SWIGLU: T [M][ldu]
+    void* uout; int F; int ldu;          // EP_SWIGLU: T, M rows of ldu columns in fragment order (zero past F)
     int* err;                            // device error flags (bit 4: write past the cache)
     // EP_RESID split over ksplit workgroups per tile (ksplit > 1): every wave's raw partial tile goes to
     // part [n_tiles][waves * ksplit][MT][64] (f32x4), folded in wave order by a second kernel
@@ -105,8 +105,9 @@ struct AttnArgs {
                              // Dh / cols columns of O
     float* part;             // [B*H][splits][16*MT rows][Dh + 4]: unnormalised O, row max, row sum
     int* counter;            // [B*H][row tiles] arrival counts of the splits (zero between launches)
-    void* out;               // T (or float if out_f32) [B*q][ldo], head h at columns h*Dh..
-    int out_f32, ldo;
+    // head h at columns h*Dh..: float [B*q][ldo] if out_f32, else T in fragment order (out_rows rows of ldo)
+    void* out;
+    int out_f32, ldo, out_rows;
     int* err;                // device error flags (bit 4: read past the cache)
 };
 // `splits` x `cols` workgroups of `waves` waves per (sequence, head, 16-row tile); max_len: the
@@ -135,6 +136,7 @@ hipError_t launch_attention_rows(int dtype, int head_dim, const AttnArgs& a, hip
 hipError_t launch_embed(int dtype, const void* embed, int n_rows_emb, int d, const int* tokens, int M,
                         float* x, float* xg, const float* gain, int ldxg, float* ssq, int n_ssq, int* err,
                         hipStream_t s);
+// float rows [rows][cols] -> elements in fragment order, zero in columns cols..ld-1 (ld a multiple of 8)
 hipError_t launch_to_elem_rows(int dtype, const float* src, int rows, int cols, void* dst, int ld, hipStream_t s);
 hipError_t launch_kv_write(int dtype, void* kc, void* vc, int B, int n, int H, int Dh, int S_max,
                            const float* k, const float* v, const int* pos, hipStream_t s);
@@ -164,7 +166,7 @@ hipError_t launch_rope_table(const double* inv_freq, int S, int half, float* rop
 enum { PG_STORE = 0, PG_QKV = 1, PG_SWIGLU = 2 };
 struct PrefillGemmArgs {
     int M, N, K;
-    const void* A; int lda;
+    const void* A; int lda;       // fragment order, M rounded up to 16 rows of lda columns
     const void* W0; const void* W1; const void* W2; int n_per;
     float* C; int ldc;
     int ksplit; size_t c_part;
@@ -178,14 +180,18 @@ constexpr int kPrefillMaxSplit = 4;
 int prefill_gemm_ksplit(int M, int N, int K);
 hipError_t launch_prefill_gemm(int dtype, const PrefillGemmArgs& p, hipStream_t s);
 // Row-wise steps around the prefill GEMMs of blocks of more than 64 rows.
-// h = elem(xg / rms) with rms from the row's per-16-column sums of squares
-hipError_t launch_rms_rows(int dtype, const float* xg, int ldxg, const float* ssq, int n_ssq, int K, float eps, int M,
-                           void* h, int ldh, hipStream_t s);
+// h = elem(xg / rms) with rms from the row's per-16-column sums of squares; xg and h in fragment order
+// (M rows of ld columns; K a multiple of 8)
+hipError_t launch_rms_rows(int dtype, const float* xg, int ld, const float* ssq, int n_ssq, int K, float eps, int M,
+                           void* h, hipStream_t s);
 // x += y with y = ((y_0 + y_1) + y_2) + ..., the parts of a split contraction (parts >= 1, part p at
 // y + p * part_stride); h = elem((x o g) / rms(x)), bitwise what the residual epilogue's per-16-column
-// sums of squares and rms_rows give (rows of up to 8192 columns)
+// sums of squares and rms_rows give (rows of up to 8192 columns).  h: fragment order, M rounded up to 16 rows
 hipError_t launch_resid_norm_rows(int dtype, const float* y, int parts, size_t part_stride, int ldy, int M, int N,
                                   float* x, int ldx, const float* g, float eps, void* h, int ldh, hipStream_t s);
+// the same for layer 0: x = E[token] (ids out of range set *err bit 1 and read row 0)
+hipError_t launch_embed_norm_rows(int dtype, const void* embed, int n_rows_emb, const int* tokens, int M, int N, float* x,
+                                  const float* g, float eps, void* h, int ldh, int* err, hipStream_t s);
 
 // ---------------------------------------------------------------- verify
 hipError_t launch_verify_greedy(const float* logits, int B, int q, int V, const int* drafts, int drafts_ld,

@@ -12,7 +12,7 @@ namespace sdsat {
 // RMSNorm scale reduces).  One thread per 16-column tile, vector loads and
 // stores.  Out-of-range ids set *err and read row 0.
 template <typename T>
-__global__ void embed_kernel(const T* emb, int n_rows, int d, const int* tokens, float* x, float* xg,
+__global__ void embed_kernel(const T* emb, int n_rows, int d, const int* tokens, int M, float* x, float* xg,
                              const float* gain, int ldxg, float* ssq, int n_ssq, int* err) {
     const int m = blockIdx.y;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;   // 16-column tile
@@ -37,13 +37,12 @@ __global__ void embed_kernel(const T* emb, int n_rows, int d, const int* tokens,
     for (int j = 0; j < 16; ++j) ss += v[j] * v[j];
     if ((d & 15) == 0 && (ldxg & 3) == 0 && ((uintptr_t)gain & 15) == 0) {
         f32x4_t* xo = reinterpret_cast<f32x4_t*>(x + (size_t)m * d + 16 * t);
-        f32x4_t* go = reinterpret_cast<f32x4_t*>(xg + (size_t)m * ldxg + 16 * t);
         const f32x4_t* gi = reinterpret_cast<const f32x4_t*>(gain + 16 * t);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const f32x4_t e = f32x4_t{v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
             xo[i] = e;
-            go[i] = e * gi[i];
+            *reinterpret_cast<f32x4_t*>(xg + frag_off(m, 16 * t + 4 * i, ldxg, M)) = e * gi[i];
         }
     } else {
 #pragma unroll
@@ -51,7 +50,7 @@ __global__ void embed_kernel(const T* emb, int n_rows, int d, const int* tokens,
             const int k = 16 * t + j;
             if (k < d) {
                 x[(size_t)m * d + k] = v[j];
-                xg[(size_t)m * ldxg + k] = v[j] * gain[k];
+                xg[frag_off(m, k, ldxg, M)] = v[j] * gain[k];
             }
         }
     }
@@ -63,26 +62,34 @@ hipError_t launch_embed(int dtype, const void* embed, int n_rows_emb, int d, con
                         hipStream_t s) {
     if (dtype == 1)
         hipLaunchKernelGGL(embed_kernel<uint16_t>, dim3((n_ssq + 63) / 64, M), dim3(64), 0, s,
-                           (const uint16_t*)embed, n_rows_emb, d, tokens, x, xg, gain, ldxg, ssq, n_ssq, err);
+                           (const uint16_t*)embed, n_rows_emb, d, tokens, M, x, xg, gain, ldxg, ssq, n_ssq, err);
     else
         hipLaunchKernelGGL(embed_kernel<float>, dim3((n_ssq + 63) / 64, M), dim3(64), 0, s, (const float*)embed,
-                           n_rows_emb, d, tokens, x, xg, gain, ldxg, ssq, n_ssq, err);
+                           n_rows_emb, d, tokens, M, x, xg, gain, ldxg, ssq, n_ssq, err);
     return hipGetLastError();
 }
 
-// float rows [rows][cols] -> element rows [rows][ld], zero in columns cols..ld-1
+// float rows [rows][cols] -> elements in fragment order, zero in columns cols..ld-1; a thread per
+// 8-element chunk of a row
 template <typename T>
 __global__ void to_elem_rows_kernel(const float* src, int rows, int cols, T* dst, int ld) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)rows * ld) return;
-    const int r = (int)(i / ld), c = (int)(i % ld);
-    dst[i] = to_elem<T>(c < cols ? src[(size_t)r * cols + c] : 0.f);
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;   // (tile, chunk, row of the tile): the order of dst
+    const int per_tile = 2 * ld;                            // 16 rows x ld / 8 chunks
+    const int tile = i / per_tile, r = min(16, rows - 16 * tile);
+    if (r <= 0) return;
+    const int e = i - tile * per_tile, k = e / r * 8, m = 16 * tile + e % r;
+    if (k >= ld) return;
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = k + j < cols ? src[(size_t)m * cols + k + j] : 0.f;
+    Frag<T>::from_f32(v).store(dst + (size_t)tile * 16 * ld + (size_t)e * 8);
 }
 
 hipError_t launch_to_elem_rows(int dtype, const float* src, int rows, int cols, void* dst, int ld, hipStream_t s) {
-    const size_t n = (size_t)rows * ld;
+    if (rows < 1) return hipSuccess;
+    if (ld % 8 || ld < cols) return hipErrorInvalidValue;
+    const size_t n = (size_t)((rows + 15) / 16) * 2 * ld;
     const int blocks = (int)((n + 255) / 256);
-    if (blocks == 0) return hipSuccess;
     if (dtype == 1)
         hipLaunchKernelGGL(to_elem_rows_kernel<uint16_t>, dim3(blocks), dim3(256), 0, s, src, rows, cols,
                            (uint16_t*)dst, ld);

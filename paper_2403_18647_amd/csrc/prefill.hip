@@ -9,142 +9,204 @@
 // stores): the RMSNorm output bf16(x o g / rms), K and V, the SwiGLU product;
 // Q and the residual stream stay float.  Rotary cos / sin come from the same
 // table as the decode path.
+#include <algorithm>
+
 #include "device.h"
 #include "kernels.h"
 
 namespace sdsat {
 
-// h[m][k] = elem(xg[m][k] / rms_m), rms_m = sqrt(sum_t ssq[m][t] / K + eps).
-// Workgroup (m, chunk) writes 4 * 256 columns of row m; every thread's four
-// values are requested first, then the first wave sums the row's partials in
-// the order the decode GEMM does (lane-strided, then a wave butterfly).
+// h[m][k] = elem(xg[m][k] / rms_m), rms_m = sqrt(sum_t ssq[m][t] / K + eps),
+// xg and h in fragment order: a thread takes one 8-element chunk of a row, so
+// reads and writes are both contiguous.  A workgroup covers 256 chunks of one
+// 16-row tile; its values are requested first, then the waves sum the tile's
+// rows' partials in the order the decode GEMM does (lane-strided, then a wave
+// butterfly).
 template <typename T>
-__global__ void __launch_bounds__(256) rms_rows_kernel(const float* xg, int ldxg, const float* ssq, int n_ssq, int K,
-                                                       float eps, T* h, int ldh) {
-    __shared__ float s_inv;
-    const int m = blockIdx.x;
-    const int k0 = (blockIdx.y * 256 + threadIdx.x) * 4;
-    const float* xr = xg + (size_t)m * ldxg;
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    const bool whole = k0 + 3 < K;   // ldxg and the row start are multiples of 4 floats
-    if (whole) {
-        const float4 t = *reinterpret_cast<const float4*>(xr + k0);
-        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-    } else {
+__global__ void __launch_bounds__(256) rms_rows_kernel(const float* xg, int ld, const float* ssq, int n_ssq, int K,
+                                                       float eps, int M, T* h) {
+    __shared__ float s_inv[16];
+    const int tile = blockIdx.y, rows = min(16, M - 16 * tile);
+    const int e = blockIdx.x * 256 + threadIdx.x;   // (chunk, row of the tile)
+    const bool mine = e < rows * (K / 8);
+    const size_t off = (size_t)tile * 16 * ld + (size_t)e * 8;
+    Frag<float> v = Frag<float>::zero();
+    if (mine) v = Frag<float>::load(xg + off);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    float sq[4][4], sum[4];   // this wave's rows: wave, wave + 4, ..
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = k0 + i < K ? xr[k0 + i] : 0.f;
+    for (int j = 0; j < 4; ++j) {
+        // the first 256 partials of every row are requested together (indices clamped into the array)
+        const float* sr = ssq + (size_t)(16 * tile + min(wave + 4 * j, rows - 1)) * n_ssq;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sq[j][i] = sr[min(lane + 64 * i, n_ssq - 1)];
     }
-    if (threadIdx.x < 64) {
-        float sum = 0.f;
-        for (int col = threadIdx.x; col < n_ssq; col += 64) sum += ssq[(size_t)m * n_ssq + col];
-        sum = wave_sum(sum);
-        if (threadIdx.x == 0) s_inv = 1.0f / sqrtf(sum / (float)K + eps);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        sum[j] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[j] += lane + 64 * i < n_ssq ? sq[j][i] : 0.f;
+        if (n_ssq > 256) {
+            const float* sr = ssq + (size_t)(16 * tile + min(wave + 4 * j, rows - 1)) * n_ssq;
+            for (int col = lane + 256; col < n_ssq; col += 64) sum[j] += sr[col];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        sum[j] = wave_sum(sum[j]);
+        if (lane == 0) s_inv[wave + 4 * j] = 1.0f / sqrtf(sum[j] / (float)K + eps);
     }
     __syncthreads();
-    const float inv = s_inv;
-    T* hr = h + (size_t)m * ldh;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (k0 + i < K) hr[k0 + i] = to_elem<T>(v[i] * inv);
+    if (!mine) return;
+    const float inv = s_inv[e % rows];
+    const float x[8] = {v.lo.x * inv, v.lo.y * inv, v.lo.z * inv, v.lo.w * inv,
+                        v.hi.x * inv, v.hi.y * inv, v.hi.z * inv, v.hi.w * inv};
+    Frag<T>::from_f32(x).store(h + off);
 }
 
-// The residual add and the next RMSNorm of a large block in one pass over each
-// row: x[m] += y[m] (the sum of a split contraction's parts, in part order), then
-// h[m] = elem((x[m] o g) / rms_m).  One workgroup per row; each thread keeps
-// its columns' x o g in registers.  The sums of squares are formed per 16-column
-// group in the decode residual epilogue's butterfly and reduced in rms_rows'
-// order (lane-strided, then a wave butterfly), so h is bitwise what a separate
-// residual pass and rms_rows give.
-static constexpr int kNormRowThreads = 1024;
-static constexpr int kNormRowMaxPer = 8;   // columns per thread: rows of up to 8192
-template <typename T>
-__global__ void __launch_bounds__(kNormRowThreads) resid_norm_rows_kernel(const float* y, int parts, size_t part_stride,
-                                                                          int ldy, int N, float* x, int ldx,
-                                                                          const float* g, float eps, T* h, int ldh) {
-    constexpr int NT = kNormRowThreads, P = kNormRowMaxPer;
-    __shared__ float s_ssq[P * NT / 16];
+// One row of a large block (more than 64 rows): its new residual value and the
+// next GEMM's normalised input h[m] = elem((x[m] o g) / rms_m), in one pass.
+// EMBED: x[m] = E[token[m]] (layer 0; ids out of range set *err and read row 0);
+// otherwise x[m] += y[m], the sum of a split contraction's parts in part order.
+// One workgroup per row, four columns per thread and pass, every load issued
+// first.  The sums of squares are formed per 16-column group in the decode
+// residual epilogue's butterfly (columns c, c + 8, then + 4, + 2, + 1) and
+// reduced in rms_rows' order (lane-strided, then a wave butterfly), so h is
+// bitwise what a separate residual pass and rms_rows give.  h is in fragment
+// order, where 16 rows share each cache line: runs of 16 rows go to one XCD
+// (workgroups go to the 8 XCDs round-robin), whose L2 then merges their writes.
+static constexpr int kNormRowMaxThreads = 1024;
+static constexpr int kNormRowPasses = 2;   // rows of up to 2 x 4 x 1024 columns
+struct NormRowArgs {
+    const float* y; int parts; size_t part_stride; int ldy;   // residual update
+    const void* emb; int n_emb; const int* tokens; int* err;   // EMBED
+    int M, N; float* x; const float* g; float eps; void* h; int ldh;
+};
+template <typename T, bool EMBED>
+__global__ void __launch_bounds__(kNormRowMaxThreads) norm_rows_kernel(NormRowArgs a) {
+    constexpr int P = kNormRowPasses;
+    __shared__ float s_ssq[P * 4 * kNormRowMaxThreads / 16];
     __shared__ float s_inv;
-    const int m = blockIdx.x, t = threadIdx.x;
-    const int nch = (N + NT - 1) / NT;
-    // every load first (indices clamped into the row), then the arithmetic
-    float yv[P], xv[P], gv[P];
+    const int per = (int)gridDim.x / 8, m = ((int)blockIdx.x % 8) * per + (int)blockIdx.x / 8, t = threadIdx.x;
+    if (m >= a.M) return;
+    float* x = a.x + (size_t)m * a.N;
+    f32x4_t v[P], gv[P];
+    size_t erow = 0;
+    if constexpr (EMBED) {
+        int tok = a.tokens[m];
+        if (tok < 0 || tok >= a.n_emb) {
+            if (t == 0) atomicOr(a.err, 1);
+            tok = 0;
+        }
+        erow = (size_t)tok * a.N;
+    }
 #pragma unroll
     for (int c = 0; c < P; ++c) {
-        const int n = min(c * NT + t, N - 1);
-        yv[c] = xv[c] = gv[c] = 0.f;
-        if (c < nch) {
-            float pv[kPrefillMaxSplit];
+        const int n = min((c * (int)blockDim.x + t) * 4, a.N - 4);   // clamped into the row
+#pragma unroll
+        for (int i = 0; i < 4; ++i) gv[c][i] = a.g[n + i];
+        if constexpr (EMBED) {
+            const T* src = reinterpret_cast<const T*>(a.emb) + erow + n;
+            if constexpr (sizeof(T) == 2) {
+                const uint2 w = *reinterpret_cast<const uint2*>(src);
+                v[c] = f32x4_t{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u),
+                               __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xFFFF0000u)};
+            } else {
+                v[c] = *reinterpret_cast<const f32x4_t*>(src);
+            }
+        } else {
+            const float* y = a.y + (size_t)m * a.ldy + n;
+            f32x4_t pv[kPrefillMaxSplit];
 #pragma unroll
             for (int q = 0; q < kPrefillMaxSplit; ++q)
-                pv[q] = q < parts ? y[q * part_stride + (size_t)m * ldy + n] : 0.f;
-            yv[c] = pv[0];
+                if (q < a.parts) pv[q] = *reinterpret_cast<const f32x4_t*>(y + q * a.part_stride);
+            const f32x4_t xv = *reinterpret_cast<const f32x4_t*>(x + n);
+            v[c] = pv[0];
 #pragma unroll
             for (int q = 1; q < kPrefillMaxSplit; ++q)
-                if (q < parts) yv[c] += pv[q];
-            xv[c] = x[(size_t)m * ldx + n];
-            gv[c] = g[n];
+                if (q < a.parts) v[c] += pv[q];
+            v[c] = xv + v[c];
         }
     }
 #pragma unroll
     for (int c = 0; c < P; ++c) {
-        if (c >= nch) continue;
-        const int n = c * NT + t;
-        float ss = 0.f;
-        if (n < N) {
-            const float v = xv[c] + yv[c];
-            x[(size_t)m * ldx + n] = v;
-            xv[c] = v * gv[c];   // x o g from here on
-            ss = v * v;
+        const int n = (c * (int)blockDim.x + t) * 4;
+        f32x4_t ss = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (n < a.N) {
+            *reinterpret_cast<f32x4_t*>(x + n) = v[c];
+            ss = v[c] * v[c];
         }
-        ss += __shfl_xor(ss, 8, 64);
-        ss += __shfl_xor(ss, 4, 64);
-        ss += __shfl_xor(ss, 2, 64);
-        ss += __shfl_xor(ss, 1, 64);
-        if ((n & 15) == 0 && n < N) s_ssq[n / 16] = ss;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ss[i] += __shfl_xor(ss[i], 2, 64);
+            ss[i] += __shfl_xor(ss[i], 1, 64);
+        }
+        if ((t & 3) == 0 && n < a.N) s_ssq[n / 16] = (ss[0] + ss[2]) + (ss[1] + ss[3]);
     }
     __syncthreads();
     if (t < 64) {
-        const int n_ssq = (N + 15) / 16;
+        const int n_ssq = a.N / 16;
         float sum = 0.f;
         for (int col = t; col < n_ssq; col += 64) sum += s_ssq[col];
         sum = wave_sum(sum);
-        if (t == 0) s_inv = 1.0f / sqrtf(sum / (float)N + eps);
+        if (t == 0) s_inv = 1.0f / sqrtf(sum / (float)a.N + a.eps);
     }
     __syncthreads();
     const float inv = s_inv;
-    T* hr = h + (size_t)m * ldh;
 #pragma unroll
     for (int c = 0; c < P; ++c) {
-        const int n = c * NT + t;
-        if (c < nch && n < N) hr[n] = to_elem<T>(xv[c] * inv);
+        const int n = (c * (int)blockDim.x + t) * 4;
+        if (n >= a.N) continue;
+        const f32x4_t w = v[c] * gv[c] * inv;
+        T* h = reinterpret_cast<T*>(a.h) + frag_off(m, n, a.ldh, (a.M + 15) & ~15);
+        if constexpr (sizeof(T) == 2)
+            *reinterpret_cast<uint2*>(h) = uint2{f32x2_to_bf16x2(w[0], w[1]), f32x2_to_bf16x2(w[2], w[3])};
+        else
+            *reinterpret_cast<f32x4_t*>(h) = w;
     }
 }
 
-hipError_t launch_rms_rows(int dtype, const float* xg, int ldxg, const float* ssq, int n_ssq, int K, float eps, int M,
-                           void* h, int ldh, hipStream_t s) {
+hipError_t launch_rms_rows(int dtype, const float* xg, int ld, const float* ssq, int n_ssq, int K, float eps, int M,
+                           void* h, hipStream_t s) {
     if (M < 1) return hipSuccess;
-    if (ldxg % 4) return hipErrorInvalidValue;   // float4 row loads
-    const dim3 grid(M, (K + 1023) / 1024);
+    if (K % 8 || ld < K) return hipErrorInvalidValue;   // whole chunks
+    const dim3 grid((unsigned)((std::min(M, 16) * (K / 8) + 255) / 256), (unsigned)((M + 15) / 16));
     if (dtype == 1)
-        hipLaunchKernelGGL(rms_rows_kernel<uint16_t>, grid, dim3(256), 0, s, xg, ldxg, ssq, n_ssq, K, eps,
-                           static_cast<uint16_t*>(h), ldh);
+        hipLaunchKernelGGL(rms_rows_kernel<uint16_t>, grid, dim3(256), 0, s, xg, ld, ssq, n_ssq, K, eps, M,
+                           static_cast<uint16_t*>(h));
     else
-        hipLaunchKernelGGL(rms_rows_kernel<float>, grid, dim3(256), 0, s, xg, ldxg, ssq, n_ssq, K, eps,
-                           static_cast<float*>(h), ldh);
+        hipLaunchKernelGGL(rms_rows_kernel<float>, grid, dim3(256), 0, s, xg, ld, ssq, n_ssq, K, eps, M,
+                           static_cast<float*>(h));
+    return hipGetLastError();
+}
+
+template <bool EMBED>
+static hipError_t norm_rows(int dtype, const NormRowArgs& a, hipStream_t s) {
+    if (a.N < 16 || a.N % 16 || a.N > kNormRowPasses * 4 * kNormRowMaxThreads || a.ldh < a.N) return hipErrorInvalidValue;
+    const int per = ((a.M + 15) / 16 + 7) / 8 * 16;   // rows per XCD
+    const dim3 grid(8 * per), block(((a.N + 4 * kNormRowPasses - 1) / (4 * kNormRowPasses) + 63) / 64 * 64);
+    if (dtype == 1) hipLaunchKernelGGL((norm_rows_kernel<uint16_t, EMBED>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((norm_rows_kernel<float, EMBED>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_resid_norm_rows(int dtype, const float* y, int parts, size_t part_stride, int ldy, int M, int N,
                                   float* x, int ldx, const float* g, float eps, void* h, int ldh, hipStream_t s) {
     if (M < 1) return hipSuccess;
-    if (N < 1 || N > kNormRowMaxPer * kNormRowThreads || parts < 1 || parts > kPrefillMaxSplit) return hipErrorInvalidValue;
-    if (dtype == 1)
-        hipLaunchKernelGGL(resid_norm_rows_kernel<uint16_t>, dim3(M), dim3(kNormRowThreads), 0, s, y, parts,
-                           part_stride, ldy, N, x, ldx, g, eps, static_cast<uint16_t*>(h), ldh);
-    else
-        hipLaunchKernelGGL(resid_norm_rows_kernel<float>, dim3(M), dim3(kNormRowThreads), 0, s, y, parts, part_stride,
-                           ldy, N, x, ldx, g, eps, static_cast<float*>(h), ldh);
-    return hipGetLastError();
+    if (parts < 1 || parts > kPrefillMaxSplit || ldx != N || ldy % 4 || part_stride % 4) return hipErrorInvalidValue;
+    NormRowArgs a{};
+    a.y = y; a.parts = parts; a.part_stride = part_stride; a.ldy = ldy;
+    a.M = M; a.N = N; a.x = x; a.g = g; a.eps = eps; a.h = h; a.ldh = ldh;
+    return norm_rows<false>(dtype, a, s);
+}
+
+hipError_t launch_embed_norm_rows(int dtype, const void* embed, int n_rows_emb, const int* tokens, int M, int N, float* x,
+                                  const float* g, float eps, void* h, int ldh, int* err, hipStream_t s) {
+    if (M < 1) return hipSuccess;
+    NormRowArgs a{};
+    a.emb = embed; a.n_emb = n_rows_emb; a.tokens = tokens; a.err = err;
+    a.M = M; a.N = N; a.x = x; a.g = g; a.eps = eps; a.h = h; a.ldh = ldh;
+    return norm_rows<true>(dtype, a, s);
 }
 
 }  // namespace sdsat

@@ -67,8 +67,8 @@ struct StepLoad {
         for (int i = 0; i < NA; ++i) {
             const int c = tid + NT * i, kc = k0 + (c % CPR) * EPC, m = m0 + c / CPR;
             ka[i] = m < p.M && kc < p.K;
-            a[i] = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const T*>(p.A) + (size_t)min(m, p.M - 1) * p.lda +
-                                                     min(kc, p.K - EPC));
+            a[i] = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const T*>(p.A) +
+                                                     frag_off(min(m, p.M - 1), min(kc, p.K - EPC), p.lda, (p.M + 15) & ~15));
         }
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(64 * WM * WN) prefill_gemm_kernel(PrefillGemmA
                 const int m = m0 + r, f = n0 / 2 + i;
                 if (m >= p.M || f >= p.n_per) continue;
                 const float gate = tile[r * LDC + i], v = tile[r * LDC + BN / 2 + i];
-                static_cast<T*>(p.u)[(size_t)m * p.ldu + f] = to_elem<T>(gate / (1.0f + expf(-gate)) * v);
+                static_cast<T*>(p.u)[frag_off(m, f, p.ldu, (p.M + 15) & ~15)] = to_elem<T>(gate / (1.0f + expf(-gate)) * v);
             }
         }
     }
