@@ -101,7 +101,7 @@ struct sdsat_ctx {
     std::vector<const float*> attn_norm, ffn_norm;
     const float* final_norm = nullptr;
     // the caller's row-major weights (embed, {attn_norm, wq, wk, wv, wo, ffn_norm, w_gate, w_up, w_down} x L,
-    // final_norm, lm_head): the prefill GEMMs of large blocks read them
+    // final_norm, lm_head): the prefill GEMMs of a float model's large blocks read them
     std::vector<const void*> w_src;
     // packed weights
     std::vector<void*> w_qkv, w_o, w_gu, w_down;
@@ -338,16 +338,17 @@ int attention_layer(sdsat_ctx* c, int layer, int B, int q, const uint64_t* mask,
     return SDSAT_OK;
 }
 
-// C[M][N] (row stride ldc, float) = A[M][K] (row stride lda) . W[N][K]^T, A and W in the model's element
-// type, W the caller's row-major [out, in] weights (up to three of n_per rows each, stacked along N): the
-// matrix-core GEMM of large blocks.
+// C[M][N] (row stride ldc, float) = A[M][K] (fragment order, lda columns) . W[N][K]^T, A and W in the model's
+// element type: the matrix-core GEMM of large blocks, on the packed weights Wp (bf16) or the caller's row-major
+// [out, in] weights W (float).
 // With c_part > 0 (the offset between partial outputs, room for kPrefillMaxSplit of them) a GEMM with
 // fewer than 256 tiles and a long contraction is split (prefill_gemm_ksplit); *parts tells the caller how
 // many partials to add.
-int big_gemm(sdsat_ctx* c, int M, int N, int K, const void* A, int lda, const void* W0, const void* W1,
-             const void* W2, int n_per, float* C, int ldc, size_t c_part = 0, int* parts = nullptr) {
+int big_gemm(sdsat_ctx* c, int M, int N, int K, const void* A, int lda, const void* W, const void* Wp, int n_tiles,
+             float* C, int ldc, size_t c_part = 0, int* parts = nullptr) {
     PrefillGemmArgs p{};
-    p.M = M; p.N = N; p.K = K; p.A = A; p.lda = lda; p.W0 = W0; p.W1 = W1; p.W2 = W2; p.n_per = n_per;
+    p.M = M; p.N = N; p.K = K; p.A = A; p.lda = lda; p.W0 = W; p.n_per = N;
+    p.Wp = Wp; p.n_tiles = n_tiles; p.k_steps = lda / 32;
     p.C = C; p.ldc = ldc;
     p.ksplit = c_part ? prefill_gemm_ksplit(M, N, K) : 1;
     p.c_part = c_part;
@@ -362,6 +363,7 @@ int big_gemm_qkv(sdsat_ctx* c, int B, int q, const void* A, const void* const* w
     PrefillGemmArgs p{};
     p.M = B * q; p.N = 3 * D.d; p.K = D.d; p.A = A; p.lda = D.d_pad;
     p.W0 = w[1]; p.W1 = w[2]; p.W2 = w[3]; p.n_per = D.d; p.ksplit = 1;
+    p.Wp = c->w_qkv[l]; p.n_tiles = D.nt_qkv; p.k_steps = D.ks_d;
     p.ep = PG_QKV; p.q = q; p.H = D.H; p.Dh = D.Dh; p.S_max = D.S; p.cache_len = c->cache_len; p.rope = c->rope;
     p.qbuf = (float*)c->qbuf; p.kc = layer_k(c, l); p.vc = layer_v(c, l); p.err = c->err_flag;
     HIPCHK(c, launch_prefill_gemm(D.dtype, p, c->stream));
@@ -369,18 +371,19 @@ int big_gemm_qkv(sdsat_ctx* c, int B, int q, const void* A, const void* const* w
 }
 
 // The gate | up GEMM of a large block with SwiGLU in its epilogue: u = silu(gate) * up in the element type.
-int big_gemm_swiglu(sdsat_ctx* c, int M, const void* A, const void* w_gate, const void* w_up) {
+int big_gemm_swiglu(sdsat_ctx* c, int M, const void* A, const void* w_gate, const void* w_up, int l) {
     const Dims& D = c->D;
     PrefillGemmArgs p{};
     p.M = M; p.N = 2 * D.F; p.K = D.d; p.A = A; p.lda = D.d_pad;
     p.W0 = w_gate; p.W1 = w_up; p.n_per = D.F; p.ksplit = 1;
+    p.Wp = c->w_gu[l]; p.n_tiles = D.nt_gu; p.k_steps = D.ks_d;
     p.ep = PG_SWIGLU; p.u = c->ubuf; p.ldu = D.F_pad;
     HIPCHK(c, launch_prefill_gemm(D.dtype, p, c->stream));
     return SDSAT_OK;
 }
 
 // Block forward of a large block (B*q > kSkinnyRows rows, chain mask): linear layers as matrix-core GEMMs
-// on the caller's weights (QKV and gate | up with their RoPE / cache and SwiGLU epilogues), the rest in
+// (QKV and gate | up with their RoPE / cache and SwiGLU epilogues), the rest in
 // row-wise kernels that round where the skinny path rounds.
 int large_block_impl(sdsat_ctx* c, int B, int q, const int32_t* tokens, float* logits) {
     const Dims& D = c->D;
@@ -400,20 +403,20 @@ int large_block_impl(sdsat_ctx* c, int B, int q, const int32_t* tokens, float* l
         if (rc) return rc;
         const size_t y_part = (size_t)D.maxM * D.d;   // offset between split-K partials in c_y
         int parts = 1;
-        rc = big_gemm(c, M, D.d, D.d, c->obuf, D.d_pad, w[4], nullptr, nullptr, D.d, c->c_y, D.d, y_part, &parts);
+        rc = big_gemm(c, M, D.d, D.d, c->obuf, D.d_pad, w[4], c->w_o[l], D.nt_o, c->c_y, D.d, y_part, &parts);
         if (rc) return rc;
         HIPCHK(c, launch_resid_norm_rows(D.dtype, c->c_y, parts, y_part, D.d, M, D.d, c->x, D.d, c->ffn_norm[l], eps,
                                          c->hbuf, D.d_pad, c->stream));
-        rc = big_gemm_swiglu(c, M, c->hbuf, w[6], w[7]);
+        rc = big_gemm_swiglu(c, M, c->hbuf, w[6], w[7], l);
         if (rc) return rc;
-        rc = big_gemm(c, M, D.d, D.F, c->ubuf, D.F_pad, w[8], nullptr, nullptr, D.d, c->c_y, D.d, y_part, &parts);
+        rc = big_gemm(c, M, D.d, D.F, c->ubuf, D.F_pad, w[8], c->w_down[l], D.nt_down, c->c_y, D.d, y_part, &parts);
         if (rc) return rc;
         HIPCHK(c, launch_resid_norm_rows(D.dtype, c->c_y, parts, y_part, D.d, M, D.d, c->x, D.d,
                                          l + 1 < D.L ? c->attn_norm[l + 1] : c->final_norm, eps, c->hbuf, D.d_pad,
                                          c->stream));
     }
     if (logits) {
-        int rc = big_gemm(c, M, D.V, D.d, c->hbuf, D.d_pad, c->w_src[2 + 9 * D.L], nullptr, nullptr, D.V, logits, D.V);
+        int rc = big_gemm(c, M, D.V, D.d, c->hbuf, D.d_pad, c->w_src[2 + 9 * D.L], c->w_lm, D.nt_lm, logits, D.V);
         if (rc) return rc;
     }
     prof_end(c, evb);

@@ -167,7 +167,8 @@ enum { PG_STORE = 0, PG_QKV = 1, PG_SWIGLU = 2 };
 struct PrefillGemmArgs {
     int M, N, K;
     const void* A; int lda;       // fragment order, M rounded up to 16 rows of lda columns
-    const void* W0; const void* W1; const void* W2; int n_per;
+    const void* W0; const void* W1; const void* W2; int n_per;   // float models: the caller's matrices
+    const void* Wp; int n_tiles, k_steps;                        // bf16 models: the packed matrix (lda = 32 k_steps)
     float* C; int ldc;
     int ksplit; size_t c_part;
     int ep;
@@ -178,6 +179,10 @@ struct PrefillGemmArgs {
 };
 constexpr int kPrefillMaxSplit = 4;
 int prefill_gemm_ksplit(int M, int N, int K);
+// bf16: the workgroup tile (an index into the kernel's instances) a product of this shape takes
+int plan_prefill_mma(int M, int n_tiles, int k_steps, int ksplit);
+int prefill_mma_configs();
+hipError_t launch_prefill_mma(int cfg, const PrefillGemmArgs& p, hipStream_t s);
 hipError_t launch_prefill_gemm(int dtype, const PrefillGemmArgs& p, hipStream_t s);
 // Row-wise steps around the prefill GEMMs of blocks of more than 64 rows.
 // h = elem(xg / rms) with rms from the row's per-16-column sums of squares; xg and h in fragment order
