@@ -481,7 +481,7 @@ __global__ void __launch_bounds__(512) attn_kernel(AttnArgs a) {
     }
 }
 
-// Blocks of many rows with the chain mask (prefill chunks): one workgroup of
+// Blocks of many rows with the chain mask (prefill chunks), float models: one workgroup of
 // 8 waves per (sequence, head, 64-row tile).  The waves come in pairs per 16
 // rows: wave (r, kp) owns rows 16r .. 16r + 15 of the tile and the key blocks
 // of parity kp, and runs the per-block step above over those its rows can see;
@@ -501,14 +501,14 @@ __global__ void __launch_bounds__(64 * kRowWaves) attn_rows_kernel(AttnArgs a) {
     constexpr int NCH = 32 * DH / CH;                       // chunks per staged operand of one block
     constexpr int NT = 64 * kRowWaves, PER = 2 * NCH / NT;  // two blocks per step
     static_assert(PER * NT == 2 * NCH, "whole chunks per thread");
-    constexpr int NQF = (E == 2 ? 2 : 1) * NDS;              // Q fragments per lane (hi, and lo for bf16)
+    static_assert(E == 4, "bf16: attn_tiles_kernel");
     constexpr int KBLK = 32 * KLD, VBLK = DH * VLD;
     // [buffer][block of the step] K and V tiles; after the last step, the parity-1 partials for the merge
     constexpr int STAGE_BYTES = 2 * 2 * (KBLK + VBLK) * E;
     constexpr int MERGE_BYTES = kRowSub * (NDT * 64 * 16 + 2 * 64 * 4);
     static_assert(MERGE_BYTES <= STAGE_BYTES, "merge buffer fits the stage buffers");
     __shared__ __align__(16) unsigned char smem[STAGE_BYTES];
-    __shared__ Frag<T> s_qf[kRowSub][NQF * 64];
+    __shared__ Frag<T> s_qf[kRowSub][NDS * 64];
     T* s_stage = reinterpret_cast<T*>(smem);
     auto s_k = [&](int buf, int j) { return s_stage + (buf * 2 + j) * (KBLK + VBLK); };
     auto s_v = [&](int buf, int j) { return s_stage + (buf * 2 + j) * (KBLK + VBLK) + KBLK; };
@@ -531,7 +531,7 @@ __global__ void __launch_bounds__(64 * kRowWaves) attn_rows_kernel(AttnArgs a) {
     const int wblk = w0 < q ? (L + min(w0 + 15, q - 1) + 32) / 32 : 0;     // this subtile's last row
     const int nstep = (nblk + 1) / 2;
 
-    // the subtile's Q rows as matrix-core fragments (hi / lo) in LDS, written by its parity-0 wave;
+    // the subtile's Q rows as matrix-core fragments in LDS, written by its parity-0 wave;
     // rows past q read row q - 1
     if (kp == 0) {
         const f32x4_t* qsrc =
@@ -540,10 +540,7 @@ __global__ void __launch_bounds__(64 * kRowWaves) attn_rows_kernel(AttnArgs a) {
         for (int ds = 0; ds < NDS; ++ds) {
             const f32x4_t q0 = qsrc[ds * 8], q1 = qsrc[ds * 8 + 1];
             const float x8[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-            Frag<T> fh, fl;
-            split_frag<T>(x8, fh, fl);
-            s_qf[rs][ds * 64 + lane] = fh;
-            if constexpr (E == 2) s_qf[rs][(NDS + ds) * 64 + lane] = fl;
+            s_qf[rs][ds * 64 + lane] = Frag<T>::from_f32(x8);
         }
     }
     // Two register sets: while step i's blocks are used from LDS, step i + 1's (requested one step
@@ -630,6 +627,241 @@ __global__ void __launch_bounds__(64 * kRowWaves) attn_rows_kernel(AttnArgs a) {
         store_out<T, DH>(a, b, h, m, 16 * dt + 4 * g, (o[dt] * a0 + m_o[dt * 64 + lane] * a1) * inv);
 }
 
+// The same for bf16: one workgroup of 2 NKP waves per (sequence, head, 64-row
+// tile), wave (rs, kp) owning rows 32rs .. 32rs + 31 of the tile and the key
+// blocks with index kp mod NKP.  A wave runs two 16-row tiles against each K / V
+// fragment it reads, with its Q fragments (value and remainder) in registers,
+// so a block costs 16 KiB of LDS reads per 64 products (above: 24 KiB per 32).
+// Each step's NKP blocks go from the cache straight into LDS (no staging
+// registers) while the step before is used, one barrier per step.  V's
+// key-permuted columns are read linearly; K's rows are stored with their
+// 16-byte chunks permuted by row (the permutation is applied to the source
+// address), so 16 rows' same chunk lies in 16 different banks.  Q is read in
+// whole rows, split and turned into fragments through the second stage buffer.
+// Blocks every row of the wave sees whole skip the mask.  The parities'
+// partials are merged in order by log-sum-exp at the end, the output tiles shared
+// out over them.  Long tiles are started first.
+// Bound by the softmax's vector arithmetic beside the products (about 450
+// instructions per block and wave) and, for short prompts, by the start (Q, the
+// cache length, the first blocks).  7B, us per layer, the float kernel's design
+// (16 rows per wave, register staging) -> this: 4 x 1023 rows 252 -> 114 (NKP 2;
+// 192 with NKP 4, whose 128 KiB leave no second workgroup beside a tile's start
+// and merge), 511 rows 23.2 -> 19.1 (NKP 4), 127 rows 8.6 -> 8.9.
+template <int DH, int NKP>
+__global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
+    using T = uint16_t;
+    constexpr int NDS = DH / 32, NDT = DH / 16, NT = 128 * NKP;
+    constexpr int CPR = DH / 8;                             // 16-byte chunks per K row
+    constexpr int HALF = 32 * DH * 2, BLK = 2 * HALF;       // bytes of one block's K (or V), of both
+    constexpr int PIECES = HALF / 1024;                     // 1 KiB loads per operand and block
+    static_assert(4 * NDT * (NKP - 1) * 1024 + 4 * NKP * 512 <= 2 * NKP * BLK, "the merge fits the stage buffers");
+    __shared__ __align__(1024) unsigned char smem[2 * NKP * BLK];
+
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int rs = wave / NKP, kp = wave % NKP, c = lane & 15, g = lane >> 4;
+    const int q = a.q, n_rt = (q + 63) / 64, pairs = a.B * a.H;
+    const int rt = n_rt - 1 - (int)blockIdx.x / pairs, bh = (int)blockIdx.x % pairs;
+    const int b = bh / a.H, h = bh % a.H;
+    // the tile's Q rows (past q: row q - 1), requested before anything that waits for the cache length
+    constexpr int PER = 64 * CPR / NT;
+    f32x4_t v[PER][2];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int ch = i * NT + (int)threadIdx.x, m = min(64 * rt + ch / CPR, q - 1);
+        const f32x4_t* src = reinterpret_cast<const f32x4_t*>(a.qbuf + (((size_t)b * q + m) * a.H + h) * DH) + ch % CPR * 2;
+        v[i][0] = src[0];
+        v[i][1] = src[1];
+    }
+    const int L = a.cache_len[b];
+    if (L + q > a.S_max) {   // the host checks capacity; never read past this sequence's cache
+        if (threadIdx.x == 0) atomicOr(a.err, 4);
+        return;
+    }
+    const unsigned char* kbase = reinterpret_cast<const unsigned char*>(a.kc) + ((size_t)b * a.H + h) * a.S_max * DH * 2;
+    const unsigned char* vbase = reinterpret_cast<const unsigned char*>(a.vc) + ((size_t)b * a.H + h) * a.S_max * DH * 2;
+    const int w0 = 64 * rt + 32 * rs, Tb = L + q;
+    const int nblk = (L + min(64 * rt + 63, q - 1) + 32) / 32;            // the tile's last row
+    const int wblk = w0 < q ? (L + min(w0 + 31, q - 1) + 32) / 32 : 0;     // this wave's last row
+    const int nstep = (nblk + NKP - 1) / NKP;
+
+    // two waves load one block: PIECES / 2 KiB of its K and of its V each
+    const int lb = wave / 2;
+    uint32_t ko[PIECES / 2], lo[PIECES / 2];   // source offset in the block's K; offset in the operand's LDS
+#pragma unroll
+    for (int i = 0; i < PIECES / 2; ++i) {
+        const int piece = (wave & 1) * (PIECES / 2) + i, ch = piece * 64 + lane, row = ch / CPR;
+        const int swz = CPR == 16 ? row & 15 : (row >> 1) & 7;
+        lo[i] = (uint32_t)piece * 1024;
+        ko[i] = (uint32_t)(row * CPR + ((ch % CPR) ^ swz)) * 16;
+    }
+    auto request = [&](int step) {   // blocks past the last repeat it: in bounds, never used
+        const size_t off = (size_t)min(step * NKP + lb, nblk - 1) * HALF;
+        unsigned char* dst = smem + (step & 1) * (NKP * BLK) + lb * BLK;
+#pragma unroll
+        for (int i = 0; i < PIECES / 2; ++i) {
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kbase + off + ko[i]),
+                                             (__attribute__((address_space(3))) void*)(dst + lo[i]), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)(vbase + off + lo[i] + lane * 16),
+                (__attribute__((address_space(3))) void*)(dst + HALF + lo[i]), 16, 0, 0);
+        }
+    };
+    request(0);
+
+    // Q as bf16 value and remainder, chunks permuted by row as K's
+    auto qoff = [](int row, int ch) { return (row * CPR + (ch ^ (CPR == 16 ? row & 15 : (row >> 1) & 7))) * 16; };
+    unsigned char* s_q = smem + NKP * BLK;
+    static_assert(2 * 64 * CPR * 16 <= NKP * BLK && 64 * CPR % NT == 0, "the Q tile fits a stage buffer");
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int ch = i * NT + (int)threadIdx.x;
+        const float x8[8] = {v[i][0].x, v[i][0].y, v[i][0].z, v[i][0].w, v[i][1].x, v[i][1].y, v[i][1].z, v[i][1].w};
+        Frag<T> hi, lw;
+        split_frag<T>(x8, hi, lw);
+        hi.store(reinterpret_cast<T*>(s_q + qoff(ch / CPR, ch % CPR)));
+        lw.store(reinterpret_cast<T*>(s_q + 64 * CPR * 16 + qoff(ch / CPR, ch % CPR)));
+    }
+    __syncthreads();
+    Frag<T> qh[2][NDS], ql[2][NDS];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds) {
+            const unsigned char* src = s_q + qoff(32 * rs + 16 * t + c, 4 * ds + g);
+            qh[t][ds] = Frag<T>::load(reinterpret_cast<const T*>(src));
+            ql[t][ds] = Frag<T>::load(reinterpret_cast<const T*>(src + 64 * CPR * 16));
+        }
+    float rmax[2] = {-INFINITY, -INFINITY}, rsum[2] = {0.f, 0.f};
+    f32x4_t o[2][NDT];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) o[t][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    for (int i = 0; i < nstep; ++i) {
+        // this wave's loads of step i have landed; after the barrier everyone's have, and nobody still
+        // reads the other buffer (step i - 1's reads, or Q's, were waited for here)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(7 << 4);   // vmcnt 0, lgkmcnt 0
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (i + 1 < nstep) request(i + 1);
+        const int blk = NKP * i + kp;
+        if (blk >= wblk) continue;
+        const unsigned char* sk = smem + (i & 1) * (NKP * BLK) + kp * BLK;
+        const unsigned char* sv = sk + HALF;
+        f32x4_t s[2][2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) s[t][0] = s[t][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ds = 0; ds < NDS; ++ds)
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+                const int row = 16 * kt + c, swz = CPR == 16 ? row & 15 : (row >> 1) & 7;
+                const Frag<T> kf = Frag<T>::load(reinterpret_cast<const T*>(sk + (row * CPR + ((ds * 4 + g) ^ swz)) * 16));
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    mma(s[t][kt], kf, qh[t][ds]);
+                    mma(s[t][kt], kf, ql[t][ds]);
+                }
+            }
+        // s[t][kt][r] = S^T[key = 32 blk + 16kt + 4g + r][row w0 + 16t + c]
+        const bool whole = 32 * blk + 31 <= L + w0;   // every key is visible to every row of the wave
+        Frag<T> ph[2], pl[2];
+        float alpha[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            float sv8[8], p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sv8[e] = s[t][e / 4][e % 4] * a.scale;
+            if (!whole) {
+                const int m = w0 + 16 * t + c;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int key = 32 * blk + 16 * (e / 4) + 4 * g + e % 4;
+                    if (!(key < Tb && m < q && key <= L + m)) sv8[e] = -INFINITY;
+                }
+            }
+            float bm = fmaxf(fmaxf(fmaxf(sv8[0], sv8[1]), fmaxf(sv8[2], sv8[3])),
+                             fmaxf(fmaxf(sv8[4], sv8[5]), fmaxf(sv8[6], sv8[7])));
+            bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
+            bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
+            const float nmax = fmaxf(rmax[t], bm);
+            const float base = nmax == -INFINITY ? 0.f : nmax;   // a row that has seen no key yet
+            alpha[t] = expf(rmax[t] - base);                     // -inf: 0
+            float ps = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                p[e] = expf(sv8[e] - base);
+                ps += p[e];
+            }
+            rsum[t] = rsum[t] * alpha[t] + ps;
+            rmax[t] = nmax;
+            split_frag<T>(p, ph[t], pl[t]);
+        }
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) {
+            const Frag<T> vf = Frag<T>::load(reinterpret_cast<const T*>(sv + (16 * dt + c) * 64 + g * 16));
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                o[t][dt] *= alpha[t];
+                mma(o[t][dt], vf, ph[t]);
+                mma(o[t][dt], vf, pl[t]);
+            }
+        }
+    }
+    __syncthreads();   // the stage buffers are free
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        rsum[t] += __shfl_xor(rsum[t], 16, 64);
+        rsum[t] += __shfl_xor(rsum[t], 32, 64);
+    }
+    // the output tiles are shared out over the parities: wave kp merges tiles kp * OWN .. and leaves its
+    // partials of the others, [rs][t][dt][NKP - 1 others], and its row maxima and sums, [rs][t][kp]
+    constexpr int OWN = NDT / NKP;
+    f32x4_t* mo = reinterpret_cast<f32x4_t*>(smem) + rs * 2 * NDT * (NKP - 1) * 64 + lane;
+    float* ms = reinterpret_cast<float*>(smem + 4 * NDT * (NKP - 1) * 1024) + rs * 2 * NKP * 128 + lane;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) {
+            const int own = dt / OWN;
+            if (own != kp) mo[((t * NDT + dt) * (NKP - 1) + (kp < own ? kp : kp - 1)) * 64] = o[t][dt];
+        }
+        ms[(t * NKP + kp) * 128] = rmax[t];
+        ms[(t * NKP + kp) * 128 + 64] = rsum[t];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int m = w0 + 16 * t + c;
+        float w[NKP], gmax = -INFINITY, den = 0.f;
+#pragma unroll
+        for (int k = 0; k < NKP; ++k) {
+            w[k] = ms[(t * NKP + k) * 128];
+            gmax = fmaxf(gmax, w[k]);
+        }
+        if (m >= q) continue;   // its rows saw no key
+#pragma unroll
+        for (int k = 0; k < NKP; ++k) {
+            w[k] = w[k] == -INFINITY ? 0.f : expf(w[k] - gmax);
+            den += w[k] * ms[(t * NKP + k) * 128 + 64];
+        }
+        const float inv = 1.0f / den;
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) {
+            const int own = dt / OWN;
+            if (own != kp) continue;
+            f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < NKP; ++k)
+                acc += (k == own ? o[t][dt] : mo[((t * NDT + dt) * (NKP - 1) + (k < own ? k : k - 1)) * 64]) * w[k];
+            store_out<T, DH>(a, b, h, m, 16 * dt + 4 * g, acc * inv);
+        }
+    }
+}
+
 hipError_t launch_attention_rows(int dtype, int head_dim, const AttnArgs& a, hipStream_t s, hipEvent_t ev0,
                                  hipEvent_t ev1) {
     if (a.q < 1 || a.q > 4096 || a.mask || a.B < 1 || a.H < 1 || a.S_max < 32 || a.S_max % 32 || a.ldo % 4 ||
@@ -637,14 +869,22 @@ hipError_t launch_attention_rows(int dtype, int head_dim, const AttnArgs& a, hip
         return hipErrorInvalidValue;
     void (*kern)(AttnArgs) = nullptr;
     // float models with 128-wide heads would need more LDS than a workgroup has: attn_kernel serves them
-    if (dtype == 1) kern = head_dim == 128 ? attn_rows_kernel<uint16_t, 128> : head_dim == 64 ? attn_rows_kernel<uint16_t, 64> : nullptr;
-    else kern = head_dim == 64 ? attn_rows_kernel<float, 64> : nullptr;
+    int threads = 64 * kRowWaves;
+    const int tiles = a.B * a.H * ((a.q + 63) / 64);
+    if (dtype == 1) {
+        // at most one workgroup per compute unit: 8 waves, half the steps; else two of 4 waves share it, one's
+        // start and merge beside the other's steps
+        const bool wide = tiles <= 256;
+        if (head_dim == 128) kern = wide ? attn_tiles_kernel<128, 4> : attn_tiles_kernel<128, 2>;
+        else if (head_dim == 64) kern = wide ? attn_tiles_kernel<64, 4> : attn_tiles_kernel<64, 2>;
+        threads = wide ? 512 : 256;
+    }
+    else if (head_dim == 64) kern = attn_rows_kernel<float, 64>;
     if (!kern) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(a.B * a.H * ((a.q + 63) / 64)));
     if (ev0)
-        hipExtLaunchKernelGGL(kern, grid, dim3(64 * kRowWaves), 0, s, ev0, ev1, 0, a);
+        hipExtLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(threads), 0, s, ev0, ev1, 0, a);
     else
-        hipLaunchKernelGGL(kern, grid, dim3(64 * kRowWaves), 0, s, a);
+        hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(threads), 0, s, a);
     return hipGetLastError();
 }
 
