@@ -6,7 +6,7 @@
 //  * W is pre-packed (launch_pack) into 16-column x 32-k tiles laid out in lane
 //    order, so every wave-wide load is one contiguous 1 KiB (bf16) run and each
 //    lane's 16 bytes is directly its matrix-core B fragment.
-//  * One workgroup per column tile (4 for prefill chunks).  Its waves split the
+//  * One workgroup per column tile (3 or 4 above 16 rows).  Its waves split the
 //    contraction into contiguous slices, stream their slice with two batches of
 //    loads in flight, read the X fragments for the same steps straight from
 //    global memory (the few X rows stay in L2, in fragment order), and reduce
@@ -97,20 +97,21 @@ void launch_pack(const PackArgs& a, hipStream_t s) {
 //    narrow [d, d] / [d, F] matrices (256 tiles, one workgroup per compute
 //    unit), 4 for the wide ones; at least 4 contraction steps per wave
 //    (several tiles per workgroup, or X staged in LDS, measured slower);
-//  * blocks of more than 16 rows (batch 4 decode, prefill chunks) reload their
-//    X fragments for every weight fragment: for the wide matrices a workgroup
-//    of 4 waves takes several column tiles so that one X load feeds their
-//    matrix-core steps: 4 (M = 64: QKV 55 -> 37 us, gate/up 103 -> 62 us), or
-//    2 for two row tiles, which keeps more workgroups than compute units
-//    (batch 4 x 6 rows: QKV 192 -> 384 workgroups, 34.4 -> 31.5 us; gate/up
-//    47.5 -> 42.1 us; block 4.92 -> 4.67 ms); the narrow ones keep one tile
-//    per workgroup.  The waves per workgroup depend on the matrix shape only
-//    where block-size invariance needs it: one row tile and several column
-//    tiles both use 4 waves on the wide matrices.
+//  * blocks of more than 16 rows (batch 4 decode, prefill chunks) read more X
+//    per weight fragment: for the wide matrices a workgroup of 4 waves takes 3
+//    column tiles, so that one X load feeds 3 products and enough workgroups
+//    are left (7B QKV: 256, one per compute unit).  us with 1 / 2 / 3 / 4 tiles,
+//    7B, 24 rows: gate/up 41.0 / 39.6 / 33.5 / 45.6, QKV 25.0 / 27.4 / 25.1 /
+//    29.2, LM head 55.3 / 54.7 / 48.5 / 55.6; 44 rows: 52.1 / 43.8 / 37.0 /
+//    46.5, 31.4 / 31.5 / 26.0 / 31.6, 72.0 / 60.6 / 53.9 / 58.0; 64 rows: 60.6 /
+//    51.4 / 41.4 / 54.5, 37.0 / 38.5 / 28.4 / 34.8, 83.4 / 71.1 / 59.5 / 63.6.
+//    The narrow ones keep one tile per workgroup.  The waves per workgroup
+//    depend on the matrix shape only where block-size invariance needs it: one
+//    row tile and several column tiles both use 4 waves on the wide matrices.
 GemmPlan plan_gemm(int M, int n_tiles, int k_steps) {
     GemmPlan p;
     p.mt = (M + 15) / 16;
-    p.ntw = (p.mt > 1 && n_tiles > 512) ? (p.mt == 2 ? 2 : 4) : 1;
+    p.ntw = p.mt > 1 && n_tiles > 512 ? 3 : 1;
     int w = p.ntw > 1 ? 4 : (n_tiles <= 512 ? 8 : 4);
     while (w > 1 && k_steps < 4 * w) w /= 2;
     p.waves = w;
@@ -545,17 +546,20 @@ static hipError_t launch_mt(const GemmPlan& p, const GemmArgs& a, hipStream_t s,
         if (ev0) hipExtLaunchKernelGGL(kernel, grid, block, p.lds_bytes, s, ev0, split ? nullptr : ev1, 0, a);
         else hipLaunchKernelGGL(kernel, grid, block, p.lds_bytes, s, a);
     };
-    switch (p.mt * 10 + p.ntw) {
-        case 11: go(gemm_kernel<T, EP, 1, 1, XF>); break;
-        case 21: go(gemm_kernel<T, EP, 2, 1, XF>); break;
-        case 31: go(gemm_kernel<T, EP, 3, 1, XF>); break;
-        case 41: go(gemm_kernel<T, EP, 4, 1, XF>); break;
-        case 22: go(gemm_kernel<T, EP, 2, 2, XF>); break;
-        case 24: go(gemm_kernel<T, EP, 2, 4, XF>); break;
-        case 34: go(gemm_kernel<T, EP, 3, 4, XF>); break;
-        case 44: go(gemm_kernel<T, EP, 4, 4, XF>); break;
-        default: return hipErrorInvalidValue;
-    }
+    // several row tiles: element-type rows only; several column tiles: 3, or 4 of a split residual GEMM
+    constexpr int NW = EP == EP_RESID ? 4 : 3;
+    if (p.mt == 1 && p.ntw == 1) go(gemm_kernel<T, EP, 1, 1, XF>);
+    else if constexpr (!XF) {
+        switch (p.mt * 10 + p.ntw) {
+            case 21: go(gemm_kernel<T, EP, 2, 1, false>); break;
+            case 31: go(gemm_kernel<T, EP, 3, 1, false>); break;
+            case 41: go(gemm_kernel<T, EP, 4, 1, false>); break;
+            case 20 + NW: go(gemm_kernel<T, EP, 2, NW, false>); break;
+            case 30 + NW: go(gemm_kernel<T, EP, 3, NW, false>); break;
+            case 40 + NW: go(gemm_kernel<T, EP, 4, NW, false>); break;
+            default: return hipErrorInvalidValue;
+        }
+    } else return hipErrorInvalidValue;
     if constexpr (EP == EP_RESID && !XF) {
         if (split) {
             const hipError_t e = hipGetLastError();

@@ -38,7 +38,7 @@ void launch_pack(const PackArgs& a, hipStream_t s);
 size_t packed_elems(int n_tiles, int k_steps);
 
 // ---------------------------------------------------------------- skinny GEMM
-// One workgroup per 16-column tile (or 4 tiles for prefill chunks); its waves
+// One workgroup per 16-column tile (3 or 4 tiles for blocks of more than 16 rows); its waves
 // split the contraction and reduce through LDS.  X is stored in fragment order
 // (device.h, frag_off: M rows of ldx columns, the 32-padded contraction length)
 // and read straight from global memory as matrix-core fragments, either
