@@ -119,7 +119,7 @@ struct sdsat_ctx {
     float* attn_part = nullptr;
     size_t attn_part_floats = 0;
     int* attn_ctr = nullptr;      // attention split arrival counters (zero between launches)
-    float* gemm_part = nullptr;   // partial tiles of split residual GEMMs
+    float* gemm_part = nullptr;   // partial rows of split residual GEMMs
     int* cache_len = nullptr; int* err_flag = nullptr; int* verify_cnt = nullptr;
     // generation buffers
     int *tok1 = nullptr, *out1 = nullptr, *out2 = nullptr, *n_accept = nullptr, *pending = nullptr;
@@ -130,6 +130,7 @@ struct sdsat_ctx {
     float* logits = nullptr;
     // large blocks (more than kSkinnyRows rows): normalised rows (element type) and float GEMM outputs
     void* hbuf = nullptr; float* c_y = nullptr;
+    bool h_ready = false;   // within one block forward: hbuf holds the next GEMM's normalised input
     int* h_pin = nullptr;   // pinned host staging
     size_t h_pin_ints = 0;
     int* h_rec = nullptr;      // pinned host copy of the loop records
@@ -278,7 +279,12 @@ int run_gemm(sdsat_ctx* c, int kind, int ep, int M, int n_tiles, int k_steps, in
     a.ksplit = p.ksplit; a.part = c->gemm_part;
     hipEvent_t e0, e1;
     prof_pair(c, kind, &e0, &e1);
-    HIPCHK(c, launch_gemm(c->D.dtype, ep, p, a, c->stream, e0, e1));
+    HIPCHK(c, launch_gemm(c->D.dtype, ep, p, a, c->stream, e0, p.ksplit > 1 ? nullptr : e1));
+    if (p.ksplit > 1) {   // adds the partials, updates the residual and leaves the normalised rows in hbuf
+        HIPCHK(c, launch_fold_norm_rows(c->D.dtype, c->gemm_part, p.waves * p.ksplit, M, N, a.resid, a.gnext,
+                                        c->cfg.rms_eps, c->hbuf, c->D.d_pad, c->stream, e1));
+    }
+    if (ep == EP_RESID) c->h_ready = p.ksplit > 1;
     return SDSAT_OK;
 }
 
@@ -437,8 +443,13 @@ int forward_block_impl(sdsat_ctx* c, int B, int q, const int32_t* tokens, const 
     // at 13B's 11 rows QKV also loses (6.86 -> 7.14 ms).  A small model's GEMMs
     // (one round of workgroups) save the launch: tiny decoder, 6 rows, gate/up
     // 3.8 + 3.4 us -> 6.0 us, LM head 3.3 + 3.4 us -> 5.4 us.
+    // Behind a split residual GEMM its row kernel has left the rounded rows already.
     auto norm_input = [&](GemmArgs& g, int float_rows, int n_tiles) -> int {
         g.ldx = D.d_pad;
+        if (c->h_ready) {
+            g.xa = c->hbuf;
+            return SDSAT_OK;
+        }
         if (M <= (n_tiles <= kFloatTiles ? kQkvFloatRows : float_rows)) {
             g.xf = c->xg; g.ssq = c->ssq; g.n_ssq = D.n_ssq; g.eps = c->cfg.rms_eps;
             return SDSAT_OK;
@@ -452,6 +463,7 @@ int forward_block_impl(sdsat_ctx* c, int B, int q, const int32_t* tokens, const 
     prof_begin(c, logits ? PK_BLOCK : PK_PREFILL, &evb);
     HIPCHK(c, launch_embed(D.dtype, c->embed, D.V + D.A, D.d, tokens, M, c->x, c->xg, c->attn_norm[0], D.d_pad,
                            c->ssq, D.n_ssq, c->err_flag, c->stream));
+    c->h_ready = false;
     for (int l = 0; l < D.L; ++l) {
         // attention sub-block: RMSNorm -> QKV (+RoPE, KV write) -> attention -> O (+residual);
         // xg holds x o (the gain of the RMSNorm the next GEMM applies)

@@ -23,9 +23,10 @@
 //  * Residual GEMMs whose tile count would leave some compute units a second
 //    workgroup (13B: 320 tiles on 256 units), and long narrow ones of blocks of
 //    several row tiles (four tiles per workgroup, so each row byte read feeds
-//    four), spread each tile's waves over several workgroups and fold the
-//    waves' partial tiles in a second kernel, in the same wave order
-//    (plan_gemm_resid).
+//    four), spread each tile's waves over several workgroups and leave the
+//    waves' partial rows to the row kernel that adds them, in the same wave
+//    order, updates the residual and normalises (plan_gemm_resid,
+//    launch_fold_norm_rows).
 //  * Fused epilogues, the reduced tiles shared out over the waves:
 //      EP_STORE   float output (LM-head logits)
 //      EP_QKV     RoPE on Q and K columns, Q (float) to its buffer, K and V into
@@ -125,17 +126,17 @@ GemmPlan plan_gemm(int M, int n_tiles, int k_steps) {
 // multiple of the 256 compute units (13B: 320 tiles) leave some units two
 // workgroups and the rest one.  Their tiles' waves are then spread over
 // ksplit workgroups (320 x 4 = 1280 workgroups of 2 waves, 5 per unit); each
-// wave keeps its slice of the contraction, and a fold kernel adds the waves'
-// partial tiles in wave order, as the single workgroup's LDS reduction does,
-// so the results are the same bit for bit.  Measured at 13B, 11 rows: down
+// wave keeps its slice of the contraction, and the row kernel that follows adds
+// the waves' partials in wave order, as the single workgroup's LDS reduction
+// does, so the results are the same bit for bit.  Measured at 13B, 11 rows: down
 // (432 contraction steps) 39.4 -> 32.6 us; O (160 steps) 16.6 -> 17.1 us, its
-// waves' work too short to cover the fold kernel's launch, so it stays whole.
+// waves' work too short to pay for the partials, so it stays whole.
 // Blocks of several row tiles re-read all of their rows in every workgroup (L2 hits, but at batch
 // 4 x 6 rows the down GEMM's 528 KB of rows per workgroup outweigh its 352 KB of weights).  A narrow
 // residual GEMM with a long contraction then takes four column tiles per workgroup, so each row byte
 // feeds four tiles, and spreads each tile's wave slices over one-wave workgroups (same slices, same
 // fold order: the same values).  Measured on the 7B down GEMM: batch 4 x 6 rows 29.2 -> 27.5 us,
-// batch 8 x 6 rows 45.5 -> 34.0 us (the fold included); the O GEMM (128 steps) split the same way
+// batch 8 x 6 rows 45.5 -> 34.0 us (a fold included); the O GEMM (128 steps) split the same way
 // was slower at batch 8 and 10.
 GemmPlan plan_gemm_resid(int M, int n_tiles, int k_steps) {
     GemmPlan p = plan_gemm(M, n_tiles, k_steps);
@@ -147,7 +148,7 @@ GemmPlan plan_gemm_resid(int M, int n_tiles, int k_steps) {
         p.lds_bytes = 0;   // partial tiles go to memory
         return p;
     }
-    if (p.ntw != 1 || n_tiles <= 256 || k_steps < 256) return p;
+    if (p.ntw != 1 || n_tiles <= 256 || n_tiles > 512 || k_steps < 256) return p;   // the row kernel: 8192 columns
     auto spread = [&](int k) {   // workgroup rounds over the average, per compute unit
         const long n = (long)n_tiles * k;
         return (double)((n + 255) / 256) * 256.0 / (double)n;
@@ -474,13 +475,19 @@ __global__ void __launch_bounds__(NTW > 1 ? 256 : 512) gemm_kernel(GemmArgs a) {
         if (s + 3 * U < nks) mma_batch<T, XF, XT, MT, NTW, U>(acc, w1, x1, inv);
     }
 
-    if (split) {   // raw partial tiles of this wave, folded by gemm_fold_kernel
+    if (split) {   // raw partial rows of this wave's slice, added by the row kernel that follows
 #pragma unroll
         for (int j = 0; j < NTW; ++j) {
             if (tile0 + j >= a.n_tiles) break;
-            f32x4_t* pp = reinterpret_cast<f32x4_t*>(a.part) + ((size_t)(tile0 + j) * nwt + gw) * MT * 64 + lane;
+            const int n = (tile0 + j) * 16 + c;
+            float* pp = a.part + (size_t)gw * M * a.N + n;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) pp[mt * 64] = acc[j][mt];
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int m = 16 * mt + 4 * g + r;
+                    if (m < M && n < a.N) pp[(size_t)m * a.N] = acc[j][mt][r];
+                }
         }
         return;
     }
@@ -511,33 +518,11 @@ __global__ void __launch_bounds__(NTW > 1 ? 256 : 512) gemm_kernel(GemmArgs a) {
     }
 }
 
-// Split residual GEMM, second pass: one wave per 16 x 16 tile adds the nwt
-// waves' partial tiles in wave order (v = p0, then v += p1, p2, ...: the
-// single workgroup's LDS reduction) and runs the EP_RESID epilogue on the sum.
-template <typename T>
-__global__ void __launch_bounds__(64) gemm_fold_kernel(GemmArgs a, int nwt, int MT) {
-    // every partial is requested before the first is added, and each row tile has its own wave (7B down,
-    // 44 rows: 11.2 -> 5.7 us; a wave per column tile adding them one load at a time)
-    constexpr int MAXW = 8;
-    const int tile = blockIdx.x, mt = blockIdx.y, lane = threadIdx.x, c = lane & 15, g = lane >> 4;
-    const f32x4_t* pp = reinterpret_cast<const f32x4_t*>(a.part) + ((size_t)tile * nwt * MT + mt) * 64 + lane;
-    f32x4_t p[MAXW];
-#pragma unroll
-    for (int w = 0; w < MAXW; ++w) p[w] = pp[(size_t)min(w, nwt - 1) * MT * 64];
-    float ep_in[4], gn;
-    epilogue_inputs<EP_RESID>(a, tile, mt, c, g, ep_in, gn);
-    f32x4_t v = p[0];
-#pragma unroll
-    for (int w = 1; w < MAXW; ++w)
-        if (w < nwt) v += p[w];
-    epilogue<T, EP_RESID>(a, tile, mt, v, ep_in, gn, c, g);
-}
-
 template <typename T, int EP, bool XF>
 static hipError_t launch_mt(const GemmPlan& p, const GemmArgs& a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     const dim3 grid(p.grid), block(64 * p.waves);
     if (p.waves > (p.ntw > 1 ? 4 : 8)) return hipErrorInvalidValue;
-    const bool split = p.ksplit > 1;
+    const bool split = p.ksplit > 1;   // ev1 is then the row kernel's
     if (split && (EP != EP_RESID || !a.part || a.ksplit != p.ksplit ||
                   p.grid != (a.n_tiles + p.ntw - 1) / p.ntw * p.ksplit))
         return hipErrorInvalidValue;
@@ -560,17 +545,6 @@ static hipError_t launch_mt(const GemmPlan& p, const GemmArgs& a, hipStream_t s,
             default: return hipErrorInvalidValue;
         }
     } else return hipErrorInvalidValue;
-    if constexpr (EP == EP_RESID && !XF) {
-        if (split) {
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            const int nwt = p.waves * p.ksplit;
-            if (nwt > 8) return hipErrorInvalidValue;
-            const dim3 fgrid(a.n_tiles, p.mt);
-            if (ev0) hipExtLaunchKernelGGL(gemm_fold_kernel<T>, fgrid, dim3(64), 0, s, nullptr, ev1, 0, a, nwt, p.mt);
-            else hipLaunchKernelGGL(gemm_fold_kernel<T>, fgrid, dim3(64), 0, s, a, nwt, p.mt);
-        }
-    }
     return hipGetLastError();
 }
 

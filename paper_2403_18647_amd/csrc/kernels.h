@@ -70,8 +70,8 @@ struct GemmArgs {
     const float* rope;                   // [S_max][Dh/2][2] rotary cos, sin of position x base^(-2i/Dh)
     void* uout; int F; int ldu;          // EP_SWIGLU: T, M rows of ldu columns in fragment order (zero past F)
     int* err;                            // device error flags (bit 4: write past the cache)
-    // EP_RESID split over ksplit workgroups per tile (ksplit > 1): every wave's raw partial tile goes to
-    // part [n_tiles][waves * ksplit][MT][64] (f32x4), folded in wave order by a second kernel
+    // EP_RESID split over ksplit workgroups per tile (ksplit > 1): every wave's raw partial rows go to
+    // part [waves * ksplit][M][N], added in wave order by launch_fold_norm_rows; nothing else is written
     int ksplit; float* part;
 };
 
@@ -195,6 +195,11 @@ hipError_t launch_rms_rows(int dtype, const float* xg, int ld, const float* ssq,
 // sums of squares and rms_rows give (rows of up to 8192 columns).  h: fragment order, M rounded up to 16 rows
 hipError_t launch_resid_norm_rows(int dtype, const float* y, int parts, size_t part_stride, int ldy, int M, int N,
                                   float* x, int ldx, const float* g, float eps, void* h, int ldh, hipStream_t s);
+// The row kernel behind a split residual GEMM of a decode block (up to kFoldMaxParts partials, row stride and
+// part stride as the GEMM writes them): the same for h in the fragment order of M rows
+constexpr int kFoldMaxParts = 8;
+hipError_t launch_fold_norm_rows(int dtype, const float* part, int parts, int M, int N, float* x, const float* g, float eps,
+                                 void* h, int ldh, hipStream_t s, hipEvent_t ev1 = nullptr);
 // the same for layer 0: x = E[token] (ids out of range set *err bit 1 and read row 0)
 hipError_t launch_embed_norm_rows(int dtype, const void* embed, int n_rows_emb, const int* tokens, int M, int N, float* x,
                                   const float* g, float eps, void* h, int ldh, int* err, hipStream_t s);

@@ -11,6 +11,8 @@
 // table as the decode path.
 #include <algorithm>
 
+#include <hip/hip_ext.h>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -64,8 +66,8 @@ __global__ void __launch_bounds__(256) rms_rows_kernel(const float* xg, int ld, 
     Frag<T>::from_f32(x).store(h + off);
 }
 
-// One row of a large block (more than 64 rows): its new residual value and the
-// next GEMM's normalised input h[m] = elem((x[m] o g) / rms_m), in one pass.
+// One row of a large block (more than 64 rows), or of a decode block behind a
+// split residual GEMM: its new residual value and the next GEMM's normalised input h[m] = elem((x[m] o g) / rms_m), in one pass.
 // EMBED: x[m] = E[token[m]] (layer 0; ids out of range set *err and read row 0);
 // otherwise x[m] += y[m], the sum of a split contraction's parts in part order.
 // One workgroup per row, four columns per thread and pass, every load issued
@@ -74,20 +76,25 @@ __global__ void __launch_bounds__(256) rms_rows_kernel(const float* xg, int ld, 
 // reduced in rms_rows' order (lane-strided, then a wave butterfly), so h is
 // bitwise what a separate residual pass and rms_rows give.  h is in fragment
 // order, where 16 rows share each cache line: runs of 16 rows go to one XCD
-// (workgroups go to the 8 XCDs round-robin), whose L2 then merges their writes.
+// (workgroups go to the 8 XCDs round-robin), whose L2 then merges their writes;
+// a decode block's few rows are spread over all of them instead.  Behind the
+// split down GEMM it replaces a kernel that folded the partials and rms_rows.
 static constexpr int kNormRowMaxThreads = 1024;
 static constexpr int kNormRowPasses = 2;   // rows of up to 2 x 4 x 1024 columns
 struct NormRowArgs {
     const float* y; int parts; size_t part_stride; int ldy;   // residual update
     const void* emb; int n_emb; const int* tokens; int* err;   // EMBED
     int M, N; float* x; const float* g; float eps; void* h; int ldh;
+    int h_rows;   // rows of h's fragment order
+    int spread;   // row = workgroup index
 };
-template <typename T, bool EMBED>
+template <typename T, bool EMBED, int MAXP>
 __global__ void __launch_bounds__(kNormRowMaxThreads) norm_rows_kernel(NormRowArgs a) {
     constexpr int P = kNormRowPasses;
     __shared__ float s_ssq[P * 4 * kNormRowMaxThreads / 16];
     __shared__ float s_inv;
-    const int per = (int)gridDim.x / 8, m = ((int)blockIdx.x % 8) * per + (int)blockIdx.x / 8, t = threadIdx.x;
+    const int per = (int)gridDim.x / 8, t = threadIdx.x;
+    const int m = a.spread ? (int)blockIdx.x : ((int)blockIdx.x % 8) * per + (int)blockIdx.x / 8;
     if (m >= a.M) return;
     float* x = a.x + (size_t)m * a.N;
     f32x4_t v[P], gv[P];
@@ -116,14 +123,14 @@ __global__ void __launch_bounds__(kNormRowMaxThreads) norm_rows_kernel(NormRowAr
             }
         } else {
             const float* y = a.y + (size_t)m * a.ldy + n;
-            f32x4_t pv[kPrefillMaxSplit];
+            f32x4_t pv[MAXP];
 #pragma unroll
-            for (int q = 0; q < kPrefillMaxSplit; ++q)
+            for (int q = 0; q < MAXP; ++q)
                 if (q < a.parts) pv[q] = *reinterpret_cast<const f32x4_t*>(y + q * a.part_stride);
             const f32x4_t xv = *reinterpret_cast<const f32x4_t*>(x + n);
             v[c] = pv[0];
 #pragma unroll
-            for (int q = 1; q < kPrefillMaxSplit; ++q)
+            for (int q = 1; q < MAXP; ++q)
                 if (q < a.parts) v[c] += pv[q];
             v[c] = xv + v[c];
         }
@@ -158,7 +165,7 @@ __global__ void __launch_bounds__(kNormRowMaxThreads) norm_rows_kernel(NormRowAr
         const int n = (c * (int)blockDim.x + t) * 4;
         if (n >= a.N) continue;
         const f32x4_t w = v[c] * gv[c] * inv;
-        T* h = reinterpret_cast<T*>(a.h) + frag_off(m, n, a.ldh, (a.M + 15) & ~15);
+        T* h = reinterpret_cast<T*>(a.h) + frag_off(m, n, a.ldh, a.h_rows);
         if constexpr (sizeof(T) == 2)
             *reinterpret_cast<uint2*>(h) = uint2{f32x2_to_bf16x2(w[0], w[1]), f32x2_to_bf16x2(w[2], w[3])};
         else
@@ -180,13 +187,14 @@ hipError_t launch_rms_rows(int dtype, const float* xg, int ld, const float* ssq,
     return hipGetLastError();
 }
 
-template <bool EMBED>
-static hipError_t norm_rows(int dtype, const NormRowArgs& a, hipStream_t s) {
+template <bool EMBED, int MAXP>
+static hipError_t norm_rows(int dtype, const NormRowArgs& a, hipStream_t s, hipEvent_t ev1 = nullptr) {
     if (a.N < 16 || a.N % 16 || a.N > kNormRowPasses * 4 * kNormRowMaxThreads || a.ldh < a.N) return hipErrorInvalidValue;
     const int per = ((a.M + 15) / 16 + 7) / 8 * 16;   // rows per XCD
-    const dim3 grid(8 * per), block(((a.N + 4 * kNormRowPasses - 1) / (4 * kNormRowPasses) + 63) / 64 * 64);
-    if (dtype == 1) hipLaunchKernelGGL((norm_rows_kernel<uint16_t, EMBED>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((norm_rows_kernel<float, EMBED>), grid, block, 0, s, a);
+    const dim3 grid(a.spread ? a.M : 8 * per), block(((a.N + 4 * kNormRowPasses - 1) / (4 * kNormRowPasses) + 63) / 64 * 64);
+    auto kern = dtype == 1 ? norm_rows_kernel<uint16_t, EMBED, MAXP> : norm_rows_kernel<float, EMBED, MAXP>;
+    if (ev1) hipExtLaunchKernelGGL(kern, grid, block, 0, s, nullptr, ev1, 0, a);
+    else hipLaunchKernelGGL(kern, grid, block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -197,7 +205,17 @@ hipError_t launch_resid_norm_rows(int dtype, const float* y, int parts, size_t p
     NormRowArgs a{};
     a.y = y; a.parts = parts; a.part_stride = part_stride; a.ldy = ldy;
     a.M = M; a.N = N; a.x = x; a.g = g; a.eps = eps; a.h = h; a.ldh = ldh;
-    return norm_rows<false>(dtype, a, s);
+    a.h_rows = (M + 15) & ~15;
+    return norm_rows<false, kPrefillMaxSplit>(dtype, a, s);
+}
+
+hipError_t launch_fold_norm_rows(int dtype, const float* part, int parts, int M, int N, float* x, const float* g, float eps,
+                                 void* h, int ldh, hipStream_t s, hipEvent_t ev1) {
+    if (M < 1 || !part || parts < 1 || parts > kFoldMaxParts || ((size_t)M * N) % 4) return hipErrorInvalidValue;
+    NormRowArgs a{};
+    a.y = part; a.parts = parts; a.part_stride = (size_t)M * N; a.ldy = N;
+    a.M = M; a.N = N; a.x = x; a.g = g; a.eps = eps; a.h = h; a.ldh = ldh; a.h_rows = M; a.spread = 1;
+    return norm_rows<false, kFoldMaxParts>(dtype, a, s, ev1);
 }
 
 hipError_t launch_embed_norm_rows(int dtype, const void* embed, int n_rows_emb, const int* tokens, int M, int N, float* x,
@@ -206,7 +224,8 @@ hipError_t launch_embed_norm_rows(int dtype, const void* embed, int n_rows_emb, 
     NormRowArgs a{};
     a.emb = embed; a.n_emb = n_rows_emb; a.tokens = tokens; a.err = err;
     a.M = M; a.N = N; a.x = x; a.g = g; a.eps = eps; a.h = h; a.ldh = ldh;
-    return norm_rows<true>(dtype, a, s);
+    a.h_rows = (M + 15) & ~15;
+    return norm_rows<true, 1>(dtype, a, s);
 }
 
 }  // namespace sdsat
