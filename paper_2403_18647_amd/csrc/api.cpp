@@ -121,6 +121,7 @@ struct sdsat_ctx {
     int* attn_ctr = nullptr;      // attention split arrival counters (zero between launches)
     float* gemm_part = nullptr;   // partial rows of split residual GEMMs
     int* cache_len = nullptr; int* err_flag = nullptr; int* verify_cnt = nullptr;
+    unsigned long long* verify_best = nullptr;   // greedy verification: each row's best so far (zero between launches)
     // generation buffers
     int *tok1 = nullptr, *out1 = nullptr, *out2 = nullptr, *n_accept = nullptr, *pending = nullptr;
     int *active = nullptr, *n_commit = nullptr, *pos0 = nullptr, *adaptive = nullptr, *ptok = nullptr;
@@ -203,6 +204,7 @@ void carve(sdsat_ctx* c, Carver& cv) {
     c->cache_len = (int*)cv.take((size_t)D.maxB * 4);
     c->err_flag = (int*)cv.take(4);
     c->verify_cnt = (int*)cv.take((size_t)D.maxB * 4);
+    c->verify_best = (unsigned long long*)cv.take((size_t)D.maxM * 8);
     c->produced = (int*)cv.take((size_t)D.maxB * 4);
     c->loop_rec = (int*)cv.take((size_t)kRecLoops * D.maxB * kLoopRecCols * 4);
     const size_t bq = (size_t)D.maxB * D.maxQ;
@@ -641,6 +643,7 @@ int sdsat_init(const sdsat_config* cfg, const void* const* weights, int32_t n_we
         (void)launch_fill_i32((int*)c->ubuf, m16 * D.F_pad * D.esz / 4, 0, c->stream);
         (void)launch_fill_i32((int*)c->hbuf, m16 * D.d_pad * D.esz / 4, 0, c->stream);
         (void)launch_fill_i32(c->verify_cnt, D.maxB, 0, c->stream);
+        (void)launch_fill_i32((int*)c->verify_best, (size_t)D.maxM * 2, 0, c->stream);
         (void)launch_fill_i32(c->attn_ctr, attention_counter_ints(D.maxB, D.H, D.maxQ), 0, c->stream);
         (void)launch_fill_i32(c->cache_len, D.maxB, 0, c->stream);
         (void)launch_fill_i32(c->err_flag, 1, 0, c->stream);
@@ -708,7 +711,7 @@ int sdsat_verify_greedy(sdsat_ctx* c, int32_t batch, int32_t q, const float* d_l
     if (!d_logits || !d_tokens_out || (d_drafts && !d_n_accept))
         return fail(c, SDSAT_EINVAL, "NULL logits, tokens_out, or n_accept with drafts");
     HIPCHK(c, launch_verify_greedy(d_logits, batch, q, c->D.V, d_drafts, q - 1, d_tokens_out, d_n_accept,
-                                   c->verify_cnt, c->stream));
+                                   c->verify_best, c->verify_cnt, c->stream));
     return SDSAT_OK;
 }
 
@@ -842,7 +845,7 @@ int generate_impl(sdsat_ctx* c, int32_t batch, const int32_t* h_prompts, int32_t
                                                 seed, c->pos0, c->out1, nullptr, c->verify_cnt, c->stream));
             } else {
                 HIPCHK(c, launch_verify_greedy(c->logits, batch, q, D.V, nullptr, q - 1, c->out1, nullptr,
-                                               c->verify_cnt, c->stream));
+                                               c->verify_best, c->verify_cnt, c->stream));
             }
             HIPCHK(c, launch_commit(c->cache_len, batch, c->active, D.S, c->err_flag, c->stream));   // keep row 0
             for (int b = 0; b < batch; ++b)
@@ -872,7 +875,7 @@ int generate_impl(sdsat_ctx* c, int32_t batch, const int32_t* h_prompts, int32_t
                                                     c->tree_depth));
                 } else {
                     HIPCHK(c, launch_verify_greedy(c->logits, batch, q2, D.V, nullptr, 0, c->tree_target, nullptr,
-                                                   c->verify_cnt, c->stream));
+                                                   c->verify_best, c->verify_cnt, c->stream));
                 }
                 HIPCHK(c, launch_tree_walk(batch, q2, k, width, c->tree_tok, c->tree_target, c->active, c->out2,
                                            c->n_accept, c->tree_rows, c->pending, c->n_commit, c->stream));
@@ -890,7 +893,7 @@ int generate_impl(sdsat_ctx* c, int32_t batch, const int32_t* h_prompts, int32_t
                                                     c->stream));
                 } else {
                     HIPCHK(c, launch_verify_greedy(c->logits, batch, q, D.V, c->out1 + 1, q, c->out2, c->n_accept,
-                                                   c->verify_cnt, c->stream));
+                                                   c->verify_best, c->verify_cnt, c->stream));
                 }
                 // verification (Eq. 3): commit rows 0..m, pending = o_m
                 HIPCHK(c, launch_loop_commit(c->cache_len, batch, q, c->active, c->n_accept, c->out2, c->pending,

@@ -205,8 +205,9 @@ hipError_t launch_embed_norm_rows(int dtype, const void* embed, int n_rows_emb, 
                                   const float* g, float eps, void* h, int ldh, int* err, hipStream_t s);
 
 // ---------------------------------------------------------------- verify
+// best [B*q] and counter [B]: zero between launches
 hipError_t launch_verify_greedy(const float* logits, int B, int q, int V, const int* drafts, int drafts_ld,
-                                int* tokens_out, int* n_accept, int* counter, hipStream_t s);
+                                int* tokens_out, int* n_accept, unsigned long long* best, int* counter, hipStream_t s);
 // row_depth (optional, a draft tree; drafts must be NULL): every row is sampled with the uniform of
 // position pos0[b] + row_depth[b*q + row]
 hipError_t launch_verify_nucleus(const float* logits, int B, int q, int V, const int* drafts, int drafts_ld,

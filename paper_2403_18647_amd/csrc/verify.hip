@@ -1,9 +1,9 @@
 // Verification kernels (Section 2.1.1 Eq. 3 and Section 2.1.2).
 //
-// One workgroup per logits row (b, j) reduces over the vocabulary; the last
-// workgroup of sequence b to finish (device-scope counter) then scans the rows
-// for the accepted prefix: m = number of leading j >= 1 with
-// drafts[b][j-1] == token[b][j-1].
+// One workgroup per logits row (b, j) -- greedy: per chunk of a row -- reduces
+// over the vocabulary; the last workgroup of sequence b to finish (device-scope
+// counter) then scans the rows for the accepted prefix: m = number of leading
+// j >= 1 with drafts[b][j-1] == token[b][j-1].
 //
 // Greedy: arg-max with ties to the lowest id.
 // Nucleus: float64 arithmetic on z = logit / T.  Optional top-k (ties keep
@@ -16,6 +16,8 @@
 // cumulative mass exceeds u * S(K*), with the cumulative sums formed by a
 // block-wide prefix scan in id order.  All sums use a fixed reduction order,
 // so results are reproducible run to run.
+#include <algorithm>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -24,6 +26,12 @@ namespace sdsat {
 // ---------------------------------------------------------------- helpers
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
     return v > bv || (v == bv && i < bi);
+}
+
+__device__ __forceinline__ uint32_t order_key(float f) {
+    uint32_t u = __float_as_uint(f);
+    if (u == 0x80000000u) u = 0u;   // -0 and +0 compare equal
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
 template <int NT>
@@ -96,21 +104,97 @@ __device__ void finish_sequence(int b, int q, const int* drafts, int drafts_ld, 
     counter[b] = 0;
 }
 
-__global__ void __launch_bounds__(1024) verify_greedy_kernel(const float* logits, int q, int V, const int* drafts,
-                                                             int drafts_ld, int* tokens_out, int* n_accept,
-                                                             int* counter) {
-    __shared__ float s_val[16];
-    __shared__ int s_idx[16];
-    const int row = blockIdx.x, b = row / q;
-    const int t = block_argmax<1024>(logits + (size_t)row * V, V, s_val, s_idx);
-    if (threadIdx.x == 0) tokens_out[row] = t;
-    finish_sequence(b, q, drafts, drafts_ld, tokens_out, n_accept, counter);
+// Greedy: each row is cut into chunks of at most kGreedyChunk ids, one workgroup
+// each (a row in one workgroup is bound by what one compute unit pulls from
+// memory, about 40 GB/s: 32016 ids take 3 us of the launch's 10).  A chunk's
+// arg-max is merged into best[row] by a device-scope atomic max over (value as
+// an order-preserving key, then the complement of the id: ties go to the lower
+// id), the workgroup counts itself done, and the sequence's last one writes its
+// tokens and accepted prefix and leaves best and the count zero for the next
+// launch.  The atomics are performed at the device's coherence point and waited
+// for, so no fence is needed.
+// us: 1 x 6 rows of 32016 ids 10.5 -> 5.5.
+static constexpr int kGreedyNT = 256;
+static constexpr int kGreedyChunk = kGreedyNT * 32;   // 8 vector loads per thread, all in flight
+__global__ void __launch_bounds__(kGreedyNT) verify_greedy_kernel(const float* logits, int q, int V, int chunk, int n_chunks,
+                                                                  const int* drafts, int drafts_ld, int* tokens_out,
+                                                                  int* n_accept, unsigned long long* best, int* counter) {
+    __shared__ float s_val[kGreedyNT / 64];
+    __shared__ int s_idx[kGreedyNT / 64];
+    __shared__ int s_last, s_miss;
+    const int row = blockIdx.x / n_chunks, lo = (int)(blockIdx.x % n_chunks) * chunk, b = row / q;
+    const float* lg = logits + (size_t)row * V + lo;
+    const int n = min(chunk, V - lo);
+    float bv = -INFINITY;
+    int bi = 0x7fffffff;
+    if ((V & 3) == 0) {   // then n and lo are multiples of 4 too
+        constexpr int PF = 8;
+        const float4* r4 = reinterpret_cast<const float4*>(lg);
+        const int n4 = n / 4;
+        for (int i0 = threadIdx.x; i0 < n4; i0 += kGreedyNT * PF) {
+            float4 v[PF];
+#pragma unroll
+            for (int p = 0; p < PF; ++p) v[p] = r4[min(i0 + p * kGreedyNT, n4 - 1)];
+#pragma unroll
+            for (int p = 0; p < PF; ++p) {
+                const int i = i0 + p * kGreedyNT;
+                if (i >= n4) break;
+                if (better(v[p].x, 4 * i, bv, bi)) { bv = v[p].x; bi = 4 * i; }
+                if (better(v[p].y, 4 * i + 1, bv, bi)) { bv = v[p].y; bi = 4 * i + 1; }
+                if (better(v[p].z, 4 * i + 2, bv, bi)) { bv = v[p].z; bi = 4 * i + 2; }
+                if (better(v[p].w, 4 * i + 3, bv, bi)) { bv = v[p].w; bi = 4 * i + 3; }
+            }
+        }
+    } else {
+        for (int i = threadIdx.x; i < n; i += kGreedyNT) {
+            const float v = lg[i];
+            if (better(v, i, bv, bi)) { bv = v; bi = i; }
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(bv, o, 64);
+        const int oi = __shfl_xor(bi, o, 64);
+        if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+    }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (lane == 0) { s_val[wave] = bv; s_idx[wave] = bi; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kGreedyNT / 64; ++w)
+            if (better(s_val[w], s_idx[w], bv, bi)) { bv = s_val[w]; bi = s_idx[w]; }
+        if (bi != 0x7fffffff) {   // else no id compares (all NaN): best stays 0, token 0
+            const unsigned long long key = ((unsigned long long)order_key(bv) << 32) | (uint32_t)~(uint32_t)(lo + bi);
+            (void)__hip_atomic_fetch_max(&best[row], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_s_waitcnt(0);   // performed before the count is raised
+        s_last = __hip_atomic_fetch_add(&counter[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == q * n_chunks - 1;
+        s_miss = q;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    for (int j = threadIdx.x; j < q; j += kGreedyNT) {
+        unsigned long long* p = &best[(size_t)b * q + j];
+        const unsigned long long v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int t = v ? (int)~(uint32_t)v : 0;
+        tokens_out[(size_t)b * q + j] = t;
+        // row j's token against draft j + 1
+        if (drafts && j + 1 < q && drafts[(size_t)b * drafts_ld + j] != t) atomicMin(&s_miss, j + 1);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (n_accept) n_accept[b] = drafts ? s_miss - 1 : 0;
+        __hip_atomic_store(&counter[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 hipError_t launch_verify_greedy(const float* logits, int B, int q, int V, const int* drafts, int drafts_ld,
-                                int* tokens_out, int* n_accept, int* counter, hipStream_t s) {
-    hipLaunchKernelGGL(verify_greedy_kernel, dim3(B * q), dim3(1024), 0, s, logits, q, V, drafts, drafts_ld,
-                       tokens_out, n_accept, counter);
+                                int* tokens_out, int* n_accept, unsigned long long* best, int* counter, hipStream_t s) {
+    const int n_chunks = std::min((V + kGreedyChunk - 1) / kGreedyChunk, 16);   // longer rows loop
+    const int chunk = ((V + n_chunks - 1) / n_chunks + 3) / 4 * 4;
+    hipLaunchKernelGGL(verify_greedy_kernel, dim3(B * q * n_chunks), dim3(kGreedyNT), 0, s, logits, q, V, chunk, n_chunks,
+                       drafts, drafts_ld, tokens_out, n_accept, best, counter);
     return hipGetLastError();
 }
 
@@ -131,12 +215,6 @@ __device__ __forceinline__ double readlane_d(double v, int lane) {
     const int2 p = __builtin_bit_cast(int2, v);
     return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(p.x, lane),
                                                 __builtin_amdgcn_readlane(p.y, lane)));
-}
-
-__device__ __forceinline__ uint32_t order_key(float f) {
-    uint32_t u = __float_as_uint(f);
-    if (u == 0x80000000u) u = 0u;   // -0 and +0 compare equal
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
 __device__ __forceinline__ float key_value(uint32_t k) {
