@@ -211,6 +211,14 @@ static constexpr int kBins = 16;    // radix digits of 4 bits
 static_assert(kBins % kWaves == 0, "digit totals: each wave sums kBins / kWaves digits");
 static constexpr int kArgNT = 1024; // threads of the arg-max-only tree kernel
 
+__device__ __forceinline__ uint32_t shfl_xor_any(uint32_t v, int o) { return (uint32_t)__shfl_xor((int)v, o, 64); }
+__device__ __forceinline__ uint64_t shfl_xor_any(uint64_t v, int o) {
+    return ((uint64_t)shfl_xor_any((uint32_t)(v >> 32), o) << 32) | shfl_xor_any((uint32_t)v, o);
+}
+__device__ __forceinline__ uint32_t readlane_u(uint32_t v, int lane) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
+}
+
 __device__ __forceinline__ double readlane_d(double v, int lane) {
     const int2 p = __builtin_bit_cast(int2, v);
     return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(p.x, lane),
@@ -428,16 +436,101 @@ __device__ __forceinline__ uint32_t radix_threshold(const uint32_t (&keys)[kCPT]
     return prefix;
 }
 
+// exclusive prefix sum of one int per thread, thread order, and the block's total
+__device__ int block_exscan_total_i(int v, int* s_buf, int* total) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int inc = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += t;
+    }
+    if (lane == 63) s_buf[wave] = inc;
+    __syncthreads();
+    int base = 0, sum = 0;
+    for (int w = 0; w < kWaves; ++w) {
+        base += w < wave ? s_buf[w] : 0;
+        sum += s_buf[w];
+    }
+    __syncthreads();
+    *total = sum;
+    return base + inc - v;
+}
+
+// The digits from `shift` down (the bits above it are known to be prefix's).
+// Once at most 64 ids share the prefix (12 or 16 bits leave a few dozen of
+// 32016) they are gathered in id order and one wave settles the rest: lane i
+// sums the weights of the candidates with keys at least its own, in candidate
+// order, and the threshold is the largest key whose sum reaches the goal.
+// w_of(i) gives the thread's i-th id's weight (0 for ids outside the kept set).
+template <int N, typename WeightFn>
+__device__ __forceinline__ uint32_t radix_refine(const uint32_t (&keys)[N], Bits kept, WeightFn w_of, double goal,
+                                    uint32_t prefix, int shift, double* hist, double* s_tot, int* s_i, double* mass) {
+    double above = 0.0, at = 0.0;
+#pragma unroll 1
+    for (; shift >= 0; shift -= 4) {
+        const uint32_t hi = shift == 28 ? 0u : 0xFFFFFFFFu << (shift + 4);
+        radix_clear(hist);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (!((kept >> i) & 1u)) continue;
+            const uint32_t key = keys[i];
+            if ((key & hi) != (prefix & hi)) continue;
+            radix_add(hist, key, shift, w_of(i));
+        }
+        radix_pick(hist, s_tot, shift, goal, prefix, above, at);
+        if (shift > 20 || shift == 0) continue;
+        const uint32_t in = 0xFFFFFFFFu << shift;
+        int cnt = 0, total;
+#pragma unroll
+        for (int i = 0; i < N; ++i) cnt += ((kept >> i) & 1u) && (keys[i] & in) == prefix;
+        int slot = block_exscan_total_i(cnt, s_i, &total);
+        if (total > 64) continue;
+        double* s_w = hist;                                      // [64] weights
+        uint32_t* s_k = reinterpret_cast<uint32_t*>(hist + 64);   // [64] keys
+        if (cnt) {
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                if (((kept >> i) & 1u) && (keys[i] & in) == prefix) { s_k[slot] = keys[i]; s_w[slot] = w_of(i); ++slot; }
+        }
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            const int lane = threadIdx.x;
+            const uint32_t k = lane < total ? s_k[lane] : 0u;
+            const double w = lane < total ? s_w[lane] : 0.0;
+            double sum = above;
+            for (int c = 0; c < total; ++c) {
+                const double wc = readlane_d(w, c);
+                sum += readlane_u(k, c) >= k ? wc : 0.0;
+            }
+            // the largest key that reaches the goal; the smallest if rounding leaves every sum short
+            const bool ok = lane < total && sum >= goal;
+            uint32_t best = ok ? k : 0u, least = lane < total ? k : 0xFFFFFFFFu;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                best = max(best, shfl_xor_any(best, o));
+                least = min(least, shfl_xor_any(least, o));
+            }
+            if (__ballot(ok) == 0) best = least;
+            const int who = __ffsll((unsigned long long)__ballot(lane < total && k == best)) - 1;
+            const double m = readlane_d(sum, who);
+            if (lane == 0) {
+                s_tot[0] = m;
+                s_i[0] = (int)best;
+            }
+        }
+        __syncthreads();
+        *mass = s_tot[0];
+        prefix = (uint32_t)s_i[0];
+        __syncthreads();
+        return prefix;
+    }
+    *mass = at;
+    return prefix;
+}
+
 // ---- top-k of at most kSmallK ids: candidate list
 static constexpr int kSmallK = 64;
-
-__device__ __forceinline__ uint32_t shfl_xor_any(uint32_t v, int o) { return (uint32_t)__shfl_xor((int)v, o, 64); }
-__device__ __forceinline__ uint64_t shfl_xor_any(uint64_t v, int o) {
-    return ((uint64_t)shfl_xor_any((uint32_t)(v >> 32), o) << 32) | shfl_xor_any((uint32_t)v, o);
-}
-__device__ __forceinline__ uint32_t readlane_u(uint32_t v, int lane) {
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
-}
 
 // Bitonic sort of one value per lane across the wave, descending (lane 0 holds the largest).
 template <typename U>
@@ -572,12 +665,175 @@ __device__ __forceinline__ void load_keys(const float* row, int V, int id0, uint
     }
 }
 
+// e^x for x <= 0 (0 below the smallest double): x = n ln 2 + r + c with ln 2 in two parts (Cody and Waite; the
+// fused first step is exact, c is the rounding of the second), the Taylor sum of e^r to r^13 (|r| <= 0.3466:
+// the rest is below 2^-57) added to the exact head and tail of 1 + r, scaled by 2^n.  Largest and mean error
+// over 2 million arguments in (-690, 0): 0.66 and 0.250 ulp (the math library's exp, a few times the
+// instructions: 0.85 and 0.253).
+__device__ __forceinline__ double exp_neg(double x) {
+    const double n = rint(x * 1.4426950408889634);
+    const double hi = fma(-n, 0.6931471805599453, x), lo = n * 2.3190468138462996e-17;
+    const double r = hi - lo, c = (hi - r) - lo;
+    double s = 1.0 / 6227020800.0;
+    s = fma(s, r, 1.0 / 479001600.0);
+    s = fma(s, r, 1.0 / 39916800.0);
+    s = fma(s, r, 1.0 / 3628800.0);
+    s = fma(s, r, 1.0 / 362880.0);
+    s = fma(s, r, 1.0 / 40320.0);
+    s = fma(s, r, 1.0 / 5040.0);
+    s = fma(s, r, 1.0 / 720.0);
+    s = fma(s, r, 1.0 / 120.0);
+    s = fma(s, r, 1.0 / 24.0);
+    s = fma(s, r, 1.0 / 6.0);
+    s = fma(s, r, 0.5);
+    const double head = 1.0 + r, tail = r - (head - 1.0);
+    s = head + (tail + fma(r * r, s, c));
+    return x < -746.0 ? 0.0 : ldexp(s, (int)n);
+}
+
+// x / T with r = 1 / T: one Newton step on the product gives the correctly rounded quotient (Markstein),
+// in 3 operations for the division's dozen; infinities (ids past V) keep the product.
+__device__ __forceinline__ double div_by(double x, double T, double r) {
+    const double q = x * r;
+    return __builtin_isfinite(q) ? fma(fma(-q, T, x), r, q) : q;
+}
+
+// The top-p threshold over the block's candidates (N per thread, in id order), then the inverse CDF over the
+// nucleus in ascending id order.
+static constexpr int kFew = 8;
+template <int N, typename IdFn>
+__device__ __forceinline__ int finish_row(const uint32_t (&keys)[N], const double (&e)[N], Bits kept, IdFn id_of, double pE,
+                                          uint32_t prefix, int shift, double u, double* s_hist, double* s_tot, double* s_d,
+                                          int* s_i) {
+    double mass;
+    const uint32_t Kstar =
+        radix_refine<N>(keys, kept, [&](int i) { return e[i]; }, pE, prefix, shift, s_hist, s_tot, s_i, &mass);
+    double loc = 0.0;
+    Bits inN = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (((kept >> i) & 1u) && keys[i] >= Kstar) { inN |= 1u << i; loc += e[i]; }
+    const double pre = block_exscan_d(loc, s_d);
+    const double target = u * mass;
+    int cand = 0x7fffffff;
+    int last = -1;
+    double cum = pre;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if (!((inN >> i) & 1u)) continue;
+        cum += e[i];
+        last = id_of(i);
+        if (cand == 0x7fffffff && cum > target) cand = last;
+    }
+    cand = block_min_i(cand, s_i);
+    if (cand == 0x7fffffff) cand = block_max_i(last, s_i);
+    return cand;
+}
+
+// Top-p without top-k, the usual case: only the ids that can be in the nucleus are kept.  Consecutive threads
+// hold consecutive ids (32 tiles of 1024); the total mass takes every id, and
+//  * the ids below lmax - 9 T, where they hold at most (1 - p) of the mass, or
+//  * those below lmax + T (ln((1 - p) / V) - 1) otherwise (the ids at or below the threshold hold at least
+//    (1 - p) E >= 1 - p, none more than the threshold's own weight, so that weight is at least (1 - p) / V;
+//    the 1 is for rounding)
+// neither move the threshold nor are in the nucleus (std-4 logits, T 0.8, p 0.95: 1000 of 32016 are left).
+// The others are gathered in id order, kFew to a thread, and digits in which the range's ends agree need no
+// pass.  sample_row below keeps 32 ids per thread through every step; its code, unrolled for that, is
+// fetched once per launch and took most of its 66 us.  4 x 6 rows of 32016 ids: 66.1 -> 42.6 us.
+// Returns false (nothing decided) when too many ids are left.
+__device__ __forceinline__ bool sample_row_few(const float* row, int V, double T, double p, double u, double* s_hist,
+                                               double* s_tot, double* s_d, int* s_i, float* s_f, int* out) {
+    __shared__ int s_cnt[kCPT * kWaves];
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const __amdgpu_buffer_rsrc_t rs = buf_rsrc(row, (uint32_t)V * 4);   // reads past V are not made
+    float v[kCPT];
+#pragma unroll
+    for (int i = 0; i < kCPT; ++i)
+        v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, t * 4, i * (kNT * 4), 0));
+    uint32_t kmax = 0;
+#pragma unroll
+    for (int i = 0; i < kCPT; ++i) {
+        if (i * kNT + t >= V) v[i] = -INFINITY;
+        kmax = max(kmax, order_key(v[i]));
+    }
+    const float lmax = block_max_f(key_value(kmax), s_f);
+    const double r = 1.0 / T, zmax = (double)lmax / T;
+    const uint32_t kh = order_key(lmax), k9 = order_key((float)((double)lmax - 9.0 * T));
+    auto weight = [&](uint32_t key) { return exp_neg(div_by((double)key_value(key), T, r) - zmax); };
+    double tot[2] = {0.0, 0.0};   // of all ids; of those below k9
+#pragma unroll
+    for (int i = 0; i < kCPT; ++i) {
+        const uint32_t key = order_key(v[i]);
+        const double e = i * kNT + t < V ? weight(key) : 0.0;
+        tot[0] += e;
+        tot[1] += key < k9 ? e : 0.0;
+        if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // 32 exponentials interleaved would spill
+    }
+    block_sum_d<2>(tot, s_d);
+    const double pE = p * tot[0];
+    const uint32_t kl = tot[1] <= (1.0 - p) * tot[0] * (1.0 - 1e-9)
+                            ? k9 : order_key((float)((double)lmax + T * (log((1.0 - p) / V) - 1.0)));
+    // candidates per (tile, wave), then each one's place in id order
+#pragma unroll
+    for (int i = 0; i < kCPT; ++i) {
+        const uint64_t b = __ballot(i * kNT + t < V && order_key(v[i]) >= kl);
+        if (lane == 0) s_cnt[i * kWaves + wave] = __popcll(b);
+    }
+    __syncthreads();
+    int total;
+    const int mine = t < kCPT * kWaves ? s_cnt[t] : 0;
+    const int base = block_exscan_total_i(mine, s_i, &total);
+    if (t < kCPT * kWaves) s_cnt[t] = base;
+    __syncthreads();
+    if (total > kNT * kFew) return false;
+    uint32_t* s_k = reinterpret_cast<uint32_t*>(s_hist);   // [kNT * kFew] keys, ids
+    int* s_id = reinterpret_cast<int*>(s_k + kNT * kFew);
+    static_assert(kNT * kFew * 8 <= kBins * kNT * 8, "the candidates fit the histogram's memory");
+#pragma unroll
+    for (int i = 0; i < kCPT; ++i) {
+        const bool in = i * kNT + t < V && order_key(v[i]) >= kl;
+        const uint64_t b = __ballot(in);
+        if (in) {
+            const int slot = s_cnt[i * kWaves + wave] + __popcll(b & ((1ull << lane) - 1));
+            s_k[slot] = order_key(v[i]);
+            s_id[slot] = i * kNT + t;
+        }
+    }
+    __syncthreads();
+    uint32_t fk[kFew];
+    double fe[kFew];
+    int fid[kFew];
+    Bits kept = 0;
+    const int per = (total + kNT - 1) / kNT;   // candidates per thread, a run of the list each
+#pragma unroll
+    for (int i = 0; i < kFew; ++i) {
+        const int c = t * per + i;
+        const bool in = i < per && c < total;
+        fk[i] = in ? s_k[c] : 0u;
+        fid[i] = in ? s_id[c] : 0;
+        fe[i] = 0.0;
+        if (i < per) fe[i] = in ? weight(fk[i]) : 0.0;   // per is the same in every thread
+        if (in) kept |= 1u << i;
+    }
+    __syncthreads();
+    uint32_t prefix = 0;
+    int shift = 28;
+    while (shift > 0 && (kl >> shift) == (kh >> shift)) shift -= 4;
+    if (shift < 28) prefix = kh & (0xFFFFFFFFu << (shift + 4));
+    *out = finish_row<kFew>(fk, fe, kept, [&](int i) { return fid[i]; }, pE, prefix, shift, u, s_hist, s_tot, s_d, s_i);
+    return true;
+}
+
 __device__ __forceinline__ int sample_row(const float* row, int V, double T, double p, int top_k, double u) {
     __shared__ double s_hist[kBins * kNT];   // 128 KiB: per-thread digit columns
     __shared__ double s_tot[kBins];          // digit totals (read by every thread after the last pass)
-    __shared__ double s_d[kWaves];
+    __shared__ double s_d[2 * kWaves];
     __shared__ int s_i[kWaves];
     __shared__ float s_f[kWaves];
+    if ((top_k <= 0 || top_k >= V) && p < 1.0) {
+        int tok;
+        if (sample_row_few(row, V, T, p, u, s_hist, s_tot, s_d, s_i, s_f, &tok)) return tok;
+    }
     const int id0 = threadIdx.x * kCPT;
     // ids id0 .. id0+31 as order-preserving keys (the float is recovered from the key where needed)
     uint32_t keys[kCPT];

@@ -1,0 +1,41 @@
+"""Nucleus verification where only the ids that can be in the nucleus are gathered: vocabulary edges, flat and
+peaked rows (nearly all ids left, a handful, one), ties at the threshold, -inf ids and temperatures that push
+the candidate range to either path, against the oracle's sampler on the same uniforms."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sampling as S
+from paper_2403_18647_amd import binding as B
+from paper_2403_18647_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("vocab", [3, 1000, 1025, 8193, 32016, 32768])
+@pytest.mark.parametrize("temp,p", [(0.05, 0.95), (0.8, 0.95), (1.0, 0.9), (1.0, 0.5), (3.0, 0.99), (1e30, 0.5)])
+def test_few(vocab, temp, p):
+    q = 5
+    sh = synth.small_shape(n_layers=1, vocab=vocab)
+    w = [torch.zeros(synth.tensor_shape(sh, n), device="cuda") for n in synth.tensor_names(sh)]
+    ctx = B.Context(B.make_config(sh, 1, 64, q), w)
+    rng = np.random.default_rng(vocab)
+    lg = rng.standard_normal((q, vocab)).astype(np.float32) * 4
+    lg[1] = np.round(lg[1])                     # ties everywhere, at the threshold too
+    lg[2, vocab // 3:] = -np.inf                # ids that cannot be drawn
+    lg[3] = 0.25 * lg[3]                        # flat: thousands of candidates
+    lg[4, vocab - 1] = 60.0                     # one id holds the mass
+    d = torch.from_numpy(lg).cuda()
+    pos0 = torch.tensor([17], dtype=torch.int32, device="cuda")
+    drafts = torch.zeros((1, q - 1), dtype=torch.int32, device="cuda")
+    tok = torch.empty((1, q), dtype=torch.int32, device="cuda")
+    acc = torch.empty(1, dtype=torch.int32, device="cuda")
+    for seed in range(6):
+        B.sdsat_verify_nucleus(ctx.handle, 1, q, d, drafts, temp, p, 0, seed, pos0, tok, acc)
+        torch.cuda.synchronize()
+        got = tok.cpu().numpy()[0]
+        for j in range(q):
+            want, margin = S.sample(lg[j], float(np.float32(temp)), float(np.float32(p)), 0, S.uniform(seed, 0, 17 + j))
+            # a draw this close to a decision boundary may go either way with float64 sums in another order
+            assert int(got[j]) == int(want) or margin < 1e-9, (vocab, temp, p, seed, j)
+    ctx.close()
