@@ -20,43 +20,47 @@ namespace sdsat {
 
 // h[m][k] = elem(xg[m][k] / rms_m), rms_m = sqrt(sum_t ssq[m][t] / K + eps),
 // xg and h in fragment order: a thread takes one 8-element chunk of a row, so
-// reads and writes are both contiguous.  A workgroup covers 256 chunks of one
+// reads and writes are both contiguous.  A workgroup covers 512 chunks of one
 // 16-row tile; its values are requested first, then the waves sum the tile's
 // rows' partials in the order the decode GEMM does (lane-strided, then a wave
-// butterfly).
+// butterfly).  Latency-bound: 8 waves reduce at most two rows each (with 4 waves
+// of four rows the 7B 4-layer block of 6 rows took 420 us, now 415, the 13B
+// 3-layer block of 11 rows 504, now 499).
+static constexpr int kRmsThreads = 512;
 template <typename T>
-__global__ void __launch_bounds__(256) rms_rows_kernel(const float* xg, int ld, const float* ssq, int n_ssq, int K,
+__global__ void __launch_bounds__(kRmsThreads) rms_rows_kernel(const float* xg, int ld, const float* ssq, int n_ssq, int K,
                                                        float eps, int M, T* h) {
     __shared__ float s_inv[16];
     const int tile = blockIdx.y, rows = min(16, M - 16 * tile);
-    const int e = blockIdx.x * 256 + threadIdx.x;   // (chunk, row of the tile)
+    constexpr int NW = kRmsThreads / 64, RW = 16 / NW;   // waves, rows per wave
+    const int e = blockIdx.x * kRmsThreads + threadIdx.x;   // (chunk, row of the tile)
     const bool mine = e < rows * (K / 8);
     const size_t off = (size_t)tile * 16 * ld + (size_t)e * 8;
     Frag<float> v = Frag<float>::zero();
     if (mine) v = Frag<float>::load(xg + off);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    float sq[4][4], sum[4];   // this wave's rows: wave, wave + 4, ..
+    float sq[RW][4], sum[RW];   // this wave's rows: wave, wave + NW, ..
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < RW; ++j) {
         // the first 256 partials of every row are requested together (indices clamped into the array)
-        const float* sr = ssq + (size_t)(16 * tile + min(wave + 4 * j, rows - 1)) * n_ssq;
+        const float* sr = ssq + (size_t)(16 * tile + min(wave + NW * j, rows - 1)) * n_ssq;
 #pragma unroll
         for (int i = 0; i < 4; ++i) sq[j][i] = sr[min(lane + 64 * i, n_ssq - 1)];
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < RW; ++j) {
         sum[j] = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) sum[j] += lane + 64 * i < n_ssq ? sq[j][i] : 0.f;
         if (n_ssq > 256) {
-            const float* sr = ssq + (size_t)(16 * tile + min(wave + 4 * j, rows - 1)) * n_ssq;
+            const float* sr = ssq + (size_t)(16 * tile + min(wave + NW * j, rows - 1)) * n_ssq;
             for (int col = lane + 256; col < n_ssq; col += 64) sum[j] += sr[col];
         }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < RW; ++j) {
         sum[j] = wave_sum(sum[j]);
-        if (lane == 0) s_inv[wave + 4 * j] = 1.0f / sqrtf(sum[j] / (float)K + eps);
+        if (lane == 0) s_inv[wave + NW * j] = 1.0f / sqrtf(sum[j] / (float)K + eps);
     }
     __syncthreads();
     if (!mine) return;
@@ -177,12 +181,12 @@ hipError_t launch_rms_rows(int dtype, const float* xg, int ld, const float* ssq,
                            void* h, hipStream_t s) {
     if (M < 1) return hipSuccess;
     if (K % 8 || ld < K) return hipErrorInvalidValue;   // whole chunks
-    const dim3 grid((unsigned)((std::min(M, 16) * (K / 8) + 255) / 256), (unsigned)((M + 15) / 16));
+    const dim3 grid((unsigned)((std::min(M, 16) * (K / 8) + kRmsThreads - 1) / kRmsThreads), (unsigned)((M + 15) / 16));
     if (dtype == 1)
-        hipLaunchKernelGGL(rms_rows_kernel<uint16_t>, grid, dim3(256), 0, s, xg, ld, ssq, n_ssq, K, eps, M,
+        hipLaunchKernelGGL(rms_rows_kernel<uint16_t>, grid, dim3(kRmsThreads), 0, s, xg, ld, ssq, n_ssq, K, eps, M,
                            static_cast<uint16_t*>(h));
     else
-        hipLaunchKernelGGL(rms_rows_kernel<float>, grid, dim3(256), 0, s, xg, ld, ssq, n_ssq, K, eps, M,
+        hipLaunchKernelGGL(rms_rows_kernel<float>, grid, dim3(kRmsThreads), 0, s, xg, ld, ssq, n_ssq, K, eps, M,
                            static_cast<float*>(h));
     return hipGetLastError();
 }
