@@ -32,9 +32,9 @@ __global__ void embed_kernel(const T* emb, int n_rows, int d, const int* tokens,
 #pragma unroll
         for (int j = 0; j < 16; ++j) v[j] = 16 * t + j < d ? to_f32<T>(src[j]) : 0.f;
     }
-    float ss = 0.f;
+    float ss = fmaf(v[0], v[0], v[1] * v[1]);   // order and roundings as norm_rows_kernel's for a prompt's layer 0
 #pragma unroll
-    for (int j = 0; j < 16; ++j) ss += v[j] * v[j];
+    for (int j = 2; j < 16; ++j) ss = fmaf(v[j], v[j], ss);
     if ((d & 15) == 0 && (ldxg & 3) == 0 && ((uintptr_t)gain & 15) == 0) {
         f32x4_t* xo = reinterpret_cast<f32x4_t*>(x + (size_t)m * d + 16 * t);
         const f32x4_t* gi = reinterpret_cast<const f32x4_t*>(gain + 16 * t);

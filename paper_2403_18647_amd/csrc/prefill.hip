@@ -75,10 +75,12 @@ __global__ void __launch_bounds__(kRmsThreads) rms_rows_kernel(const float* xg, 
 // EMBED: x[m] = E[token[m]] (layer 0; ids out of range set *err and read row 0);
 // otherwise x[m] += y[m], the sum of a split contraction's parts in part order.
 // One workgroup per row, four columns per thread and pass, every load issued
-// first.  The sums of squares are formed per 16-column group in the decode
-// residual epilogue's butterfly (columns c, c + 8, then + 4, + 2, + 1) and
-// reduced in rms_rows' order (lane-strided, then a wave butterfly), so h is
-// bitwise what a separate residual pass and rms_rows give.  h is in fragment
+// first.  The sums of squares are formed per 16-column group in the order of the
+// decode kernel that would form them -- the residual epilogue's butterfly
+// (columns c, c + 8, then + 4, + 2, + 1), for EMBED embed_kernel's columns in
+// turn -- and reduced in rms_rows' order (lane-strided, then a wave butterfly),
+// so h is bitwise what a separate pass and rms_rows give: a token's layer 0 is
+// the same in a prompt and in a decode block.  h is in fragment
 // order, where 16 rows share each cache line: runs of 16 rows go to one XCD
 // (workgroups go to the 8 XCDs round-robin), whose L2 then merges their writes;
 // a decode block's few rows are spread over all of them instead.  Behind the
@@ -142,17 +144,26 @@ __global__ void __launch_bounds__(kNormRowMaxThreads) norm_rows_kernel(NormRowAr
 #pragma unroll
     for (int c = 0; c < P; ++c) {
         const int n = (c * (int)blockDim.x + t) * 4;
-        f32x4_t ss = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        if (n < a.N) {
-            *reinterpret_cast<f32x4_t*>(x + n) = v[c];
-            ss = v[c] * v[c];
-        }
+        if (n < a.N) *reinterpret_cast<f32x4_t*>(x + n) = v[c];
+        if constexpr (EMBED) {   // column by column: each thread's four onto its left neighbour's sum
+            float ss = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            ss[i] += __shfl_xor(ss[i], 2, 64);
-            ss[i] += __shfl_xor(ss[i], 1, 64);
+            for (int k = 0; k < 4; ++k) {
+                const float in = __shfl_up(ss, 1, 64);
+                if ((t & 3) != k) continue;
+                ss = k ? fmaf(v[c][1], v[c][1], fmaf(v[c][0], v[c][0], in)) : fmaf(v[c][0], v[c][0], v[c][1] * v[c][1]);
+                ss = fmaf(v[c][3], v[c][3], fmaf(v[c][2], v[c][2], ss));
+            }
+            if ((t & 3) == 3 && n < a.N) s_ssq[n / 16] = ss;
+        } else {
+            f32x4_t ss = n < a.N ? v[c] * v[c] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                ss[i] += __shfl_xor(ss[i], 2, 64);
+                ss[i] += __shfl_xor(ss[i], 1, 64);
+            }
+            if ((t & 3) == 0 && n < a.N) s_ssq[n / 16] = (ss[0] + ss[2]) + (ss[1] + ss[3]);
         }
-        if ((t & 3) == 0 && n < a.N) s_ssq[n / 16] = (ss[0] + ss[2]) + (ss[1] + ss[3]);
     }
     __syncthreads();
     if (t < 64) {

@@ -1,0 +1,54 @@
+"""Layer 0's normalised rows of a large block (more than 64 rows) against the kernels of decode blocks, bit for
+bit: a token enters layer 0 the same whether it comes in a prompt or in a draft block."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2403_18647_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _unfrag(h, m, d):
+    """Rows in fragment order whose last 16-row tile holds only its real rows, as [m, d]."""
+    out = torch.empty((m, d), dtype=h.dtype, device=h.device)
+    for t in range(0, m, 16):
+        r = min(16, m - t)
+        out[t:t + r] = h[t * d:(t + r) * d].view(d // 8, r, 8).transpose(0, 1).reshape(r, d)
+    return out
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("m,d", [(65, 64), (127, 256), (70, 1088), (66, 8192)])
+def test_layer0_rows(dtype, m, d):
+    """The one-pass embedding and RMSNorm of a large block, and the decode block's two kernels."""
+    L = B.lib()
+    one = L._ZN5sdsat22launch_embed_norm_rowsEiPKviPKiiiPfPKffPviPiP12ihipStream_t
+    emb = L._ZN5sdsat12launch_embedEiPKviiPKiiPfS4_PKfiS4_iPiP12ihipStream_t
+    rms = L._ZN5sdsat15launch_rms_rowsEiPKfiS1_iifiPvP12ihipStream_t
+    P, I, F = ctypes.c_void_p, ctypes.c_int, ctypes.c_float
+    one.argtypes = [I, P, I, P, I, I, P, P, F, P, I, P, P]
+    emb.argtypes = [I, P, I, I, P, I, P, P, P, I, P, I, P, P]
+    rms.argtypes = [I, P, I, P, I, I, F, I, P, P]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    t = torch.bfloat16 if dtype else torch.float32
+    e = torch.randn((50, d), generator=g, device="cuda").to(t)
+    gain = 1 + 0.1 * torch.randn(d, generator=g, device="cuda")
+    tok = torch.randint(0, 50, (m,), generator=g, device="cuda", dtype=torch.int32)
+    m16, n_ssq = (m + 15) // 16 * 16, d // 16
+    x, x1, xg = (torch.zeros((m16, d), device="cuda") for _ in range(3))
+    ssq = torch.zeros((m, n_ssq), device="cuda")
+    h, h1 = (torch.zeros(m16 * d, device="cuda", dtype=t) for _ in range(2))
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    p = [z.data_ptr() for z in (e, tok, x, gain, h, err, x1, xg, ssq, h1)]
+    assert one(dtype, p[0], 50, p[1], m, d, p[2], p[3], 1e-5, p[4], d, p[5], st) == 0
+    assert emb(dtype, p[0], 50, d, p[1], m, p[6], p[7], p[3], d, p[8], n_ssq, p[5], st) == 0
+    assert rms(dtype, p[7], d, p[8], n_ssq, d, 1e-5, m, p[9], st) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(x, x1) and int(err) == 0
+    # the large block keeps whole 16-row tiles
+    got = h.view(m16 // 16, d // 8, 16, 8).transpose(1, 2).reshape(m16, d)[:m]
+    assert torch.equal(got, _unfrag(h1, m, d))
