@@ -357,7 +357,7 @@ __global__ void __launch_bounds__(64 * WM * WN, WM * WN >= 8 || NST * (WM * TM +
     const int grp = t / (8 * n_tiles), in = t - grp * 8 * n_tiles, gm = min(8, m_tiles - 8 * grp);
     const int mt0 = (8 * grp + in % gm) * BMT, nt0 = in / gm * BNT;
 
-    const int per = (p.k_steps + p.ksplit - 1) / p.ksplit, k0 = kpart * per;
+    const int per = ((p.k_steps + 1) / 2 + p.ksplit - 1) / p.ksplit * 2, k0 = kpart * per;   // whole 64-column pairs
     const int steps = min(p.k_steps, k0 + per) - k0;
 
     // this wave's fragments of a stage (where they do not divide, the last is repeated: the same bytes to
@@ -481,8 +481,8 @@ __global__ void __launch_bounds__(64 * WM * WN, WM * WN >= 8 || NST * (WM * TM +
                 for (int e = 0; e < 8; ++e) {
                     const float a = x[e / 4][e % 4], b = x[2 + e / 4][e % 4];
                     const float cc = cs[e / 2][2 * (e % 2)], sn = cs[e / 2][2 * (e % 2) + 1];
-                    lo[e] = a * cc - b * sn;
-                    hi[e] = a * sn + b * cc;
+                    lo[e] = fmaf(a, cc, -(b * sn));   // rounded as in the float kernel above
+                    hi[e] = fmaf(b, cc, a * sn);
                 }
                 if (sec == 0) {
                     float* q = p.qbuf + ((size_t)(16 * (mt_w + i) + r) * p.H + h) * p.Dh + pi;

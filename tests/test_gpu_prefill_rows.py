@@ -1,11 +1,13 @@
-"""Layer 0's normalised rows of a large block (more than 64 rows) against the kernels of decode blocks, bit for
-bit: a token enters layer 0 the same whether it comes in a prompt or in a draft block."""
+"""Rows of a large block (more than 64 rows), bit for bit: layer 0's normalised rows against the kernels of decode
+blocks, and RoPE's rounding.  A token enters layer 0 the same whether it comes in a prompt or in a draft block."""
 import ctypes
 
+import numpy as np
 import pytest
 import torch
 
 from paper_2403_18647_amd import binding as B
+from test_gpu_prefill_mma import QKV, STORE, _base, _frag, _launch, _operands
 
 pytestmark = pytest.mark.gpu
 
@@ -52,3 +54,42 @@ def test_layer0_rows(dtype, m, d):
     # the large block keeps whole 16-row tiles
     got = h.view(m16 // 16, d // 8, 16, 8).transpose(1, 2).reshape(m16, d)[:m]
     assert torch.equal(got, _unfrag(h1, m, d))
+
+
+@pytest.mark.parametrize("cfg", [0, 4, 7])
+def test_rope_rounding(cfg):
+    """Q and K of the QKV epilogue from the same GEMM's plain output: y1 = x1 cos - round(x2 sin) and
+    y2 = x2 cos + round(x1 sin), each one fused multiply-add."""
+    h, dh, k, m, s_max = 2, 128, 96, 129, 256
+    d, half = h * dh, dh // 2
+    x, w = _operands(m, 3 * d, k, 3)
+    t, c = torch.arange(3 * d // 16), torch.arange(16)
+    dim = 8 * (t % (dh // 16))[:, None] + torch.where(c < 8, c, half + c - 8)
+    perm = ((t // (dh // 16) * dh)[:, None] + dim).view(-1).cuda()
+    xp, wp, wq = _frag(x), _frag(w[perm]), _frag(w)
+    y = torch.empty((m, 3 * d), device="cuda")
+    a = _base(xp, m, wq, 3 * d, k, STORE)
+    a.C, a.ldc, a.c_part = y.data_ptr(), 3 * d, m * 3 * d
+    _launch(cfg, a)
+    rope = torch.randn((s_max, half, 2), device="cuda")   # any table
+    ln = torch.zeros(1, dtype=torch.int32, device="cuda")
+    qb = torch.empty((m, h, dh), device="cuda")
+    kc = torch.zeros((h, s_max, dh), device="cuda", dtype=torch.bfloat16)
+    vc = torch.zeros((h, s_max, dh), device="cuda", dtype=torch.bfloat16)
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    a = _base(xp, m, wp, 3 * d, k, QKV)
+    a.n_per, a.q, a.H, a.Dh, a.S_max = d, m, h, dh, s_max
+    a.cache_len, a.rope, a.qbuf, a.kc, a.vc, a.err = (z.data_ptr() for z in (ln, rope, qb, kc, vc, err))
+    _launch(cfg, a)
+    v = y.view(m, 3, h, dh).cpu().numpy()
+    cs, sn = (rope[:m, None, :, i].cpu().numpy() for i in (0, 1))
+
+    def fma(a, b, c):   # a b is exact in 64 bits; their sum with c rounds once more there, at 2^-53 of it
+        return (a.astype(np.float64) * b + c).astype(np.float32)
+
+    def rot(z):
+        lo, hi = z[..., :half], z[..., half:]
+        return torch.from_numpy(np.concatenate([fma(lo, cs, -(hi * sn)), fma(hi, cs, lo * sn)], -1))
+
+    assert torch.equal(qb.cpu(), rot(v[:, 0]))
+    assert torch.equal(kc[:, :m].cpu(), rot(v[:, 1]).transpose(0, 1).bfloat16())
