@@ -629,12 +629,12 @@ __global__ void __launch_bounds__(64 * kRowWaves) attn_rows_kernel(AttnArgs a) {
         store_out<T, DH>(a, b, h, m, 16 * dt + 4 * g, (o[dt] * a0 + m_o[dt * 64 + lane] * a1) * inv);
 }
 
-// The same for bf16: one workgroup of 2 NKP waves per (sequence, head, 64-row
-// tile), wave (rs, kp) owning rows 32rs .. 32rs + 31 of the tile and the key
-// blocks with index kp mod NKP.  A wave runs two 16-row tiles against each K / V
-// fragment it reads, with its Q fragments (value and remainder) in registers,
-// so a block costs 16 KiB of LDS reads per 64 products (above: 24 KiB per 32).
-// Each step's NKP blocks go from the cache straight into LDS (no staging
+// The same for bf16: one workgroup of 4 / RT pairs of waves per (sequence, head,
+// 64-row tile), wave (rs, kp) owning RT 16-row tiles from row 16 RT rs of it and
+// the key blocks of parity kp.  Its Q fragments (value and remainder) stay in
+// registers, so with RT = 2 a block costs 16 KiB of LDS reads per 64 products
+// (above: 24 KiB per 32).
+// Each step's two blocks go from the cache straight into LDS (no staging
 // registers) while the step before is used, one barrier per step.  V's
 // key-permuted columns are read linearly; K's rows are stored with their
 // 16-byte chunks permuted by row (the permutation is applied to the source
@@ -642,17 +642,21 @@ __global__ void __launch_bounds__(64 * kRowWaves) attn_rows_kernel(AttnArgs a) {
 // whole rows, split and turned into fragments through the second stage buffer.
 // Blocks every row of the wave sees whole skip the mask.  The parities'
 // partials are merged in order by log-sum-exp at the end, the output tiles shared
-// out over them.  Long tiles are started first.
+// out over them.  Long tiles are started first.  A row's sums run in the same
+// order, rounded alike (the explicit fmaf), whatever RT and in the kernel above.
 // Bound by the softmax's vector arithmetic beside the products (about 450
 // instructions per block and wave) and, for short prompts, by the start (Q, the
 // cache length, the first blocks).  7B, us per layer, the float kernel's design
-// (16 rows per wave, register staging) -> this: 4 x 1023 rows 252 -> 114 (NKP 2;
-// 192 with NKP 4, whose 128 KiB leave no second workgroup beside a tile's start
-// and merge), 511 rows 23.2 -> 19.1 (NKP 4), 127 rows 8.6 -> 8.9.
-template <int DH, int NKP>
-__global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
+// (16 rows per wave, register staging) -> this: 4 x 1023 rows 252 -> 114 (RT 2).
+// Four key parities were no faster: 192 us at 4 x 1023 rows (their 128 KiB leave
+// no second workgroup beside a tile's start and merge); the whole prompt and draft
+// block of a 4-layer 7B, us, with 4 parities of RT 2 / 2 of RT 2 / 2 of RT 1: 511
+// rows 1473 / 1486 / 1465, 127 rows 1010 / 1009 / 1001.
+template <int DH, int RT>
+__global__ void __launch_bounds__(512 / RT, 2) attn_tiles_kernel(AttnArgs a) {
     using T = uint16_t;
-    constexpr int NDS = DH / 32, NDT = DH / 16, NT = 128 * NKP;
+    constexpr int NKP = 2;                                  // key parities
+    constexpr int NDS = DH / 32, NDT = DH / 16, NG = 4 / RT, NT = 64 * NG * NKP;
     constexpr int CPR = DH / 8;                             // 16-byte chunks per K row
     constexpr int HALF = 32 * DH * 2, BLK = 2 * HALF;       // bytes of one block's K (or V), of both
     constexpr int PIECES = HALF / 1024;                     // 1 KiB loads per operand and block
@@ -681,17 +685,17 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
     }
     const unsigned char* kbase = reinterpret_cast<const unsigned char*>(a.kc) + ((size_t)b * a.H + h) * a.S_max * DH * 2;
     const unsigned char* vbase = reinterpret_cast<const unsigned char*>(a.vc) + ((size_t)b * a.H + h) * a.S_max * DH * 2;
-    const int w0 = 64 * rt + 32 * rs, Tb = L + q;
+    const int w0 = 64 * rt + 16 * RT * rs, Tb = L + q;
     const int nblk = (L + min(64 * rt + 63, q - 1) + 32) / 32;            // the tile's last row
-    const int wblk = w0 < q ? (L + min(w0 + 31, q - 1) + 32) / 32 : 0;     // this wave's last row
+    const int wblk = w0 < q ? (L + min(w0 + 16 * RT - 1, q - 1) + 32) / 32 : 0;     // this wave's last row
     const int nstep = (nblk + NKP - 1) / NKP;
 
-    // two waves load one block: PIECES / 2 KiB of its K and of its V each
-    const int lb = wave / 2;
-    uint32_t ko[PIECES / 2], lo[PIECES / 2];   // source offset in the block's K; offset in the operand's LDS
+    // NG waves load one block: PIECES / NG KiB of its K and of its V each
+    const int lb = wave / NG;
+    uint32_t ko[PIECES / NG], lo[PIECES / NG];   // source offset in the block's K; offset in the operand's LDS
 #pragma unroll
-    for (int i = 0; i < PIECES / 2; ++i) {
-        const int piece = (wave & 1) * (PIECES / 2) + i, ch = piece * 64 + lane, row = ch / CPR;
+    for (int i = 0; i < PIECES / NG; ++i) {
+        const int piece = wave % NG * (PIECES / NG) + i, ch = piece * 64 + lane, row = ch / CPR;
         const int swz = CPR == 16 ? row & 15 : (row >> 1) & 7;
         lo[i] = (uint32_t)piece * 1024;
         ko[i] = (uint32_t)(row * CPR + ((ch % CPR) ^ swz)) * 16;
@@ -700,7 +704,7 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
         const size_t off = (size_t)min(step * NKP + lb, nblk - 1) * HALF;
         unsigned char* dst = smem + (step & 1) * (NKP * BLK) + lb * BLK;
 #pragma unroll
-        for (int i = 0; i < PIECES / 2; ++i) {
+        for (int i = 0; i < PIECES / NG; ++i) {
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kbase + off + ko[i]),
                                              (__attribute__((address_space(3))) void*)(dst + lo[i]), 16, 0, 0);
             __builtin_amdgcn_global_load_lds(
@@ -724,21 +728,26 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
         lw.store(reinterpret_cast<T*>(s_q + 64 * CPR * 16 + qoff(ch / CPR, ch % CPR)));
     }
     __syncthreads();
-    Frag<T> qh[2][NDS], ql[2][NDS];
+    Frag<T> qh[RT][NDS], ql[RT][NDS];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
         for (int ds = 0; ds < NDS; ++ds) {
-            const unsigned char* src = s_q + qoff(32 * rs + 16 * t + c, 4 * ds + g);
+            const unsigned char* src = s_q + qoff(16 * (RT * rs + t) + c, 4 * ds + g);
             qh[t][ds] = Frag<T>::load(reinterpret_cast<const T*>(src));
             ql[t][ds] = Frag<T>::load(reinterpret_cast<const T*>(src + 64 * CPR * 16));
         }
-    float rmax[2] = {-INFINITY, -INFINITY}, rsum[2] = {0.f, 0.f};
-    f32x4_t o[2][NDT];
+    float rmax[RT], rsum[RT];
+    f32x4_t o[RT][NDT];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) o[t][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        rmax[t] = -INFINITY;
+        rsum[t] = 0.f;
+    }
 
     for (int i = 0; i < nstep; ++i) {
         // this wave's loads of step i have landed; after the barrier everyone's have, and nobody still
@@ -753,9 +762,9 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
         if (blk >= wblk) continue;
         const unsigned char* sk = smem + (i & 1) * (NKP * BLK) + kp * BLK;
         const unsigned char* sv = sk + HALF;
-        f32x4_t s[2][2];
+        f32x4_t s[RT][2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) s[t][0] = s[t][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < RT; ++t) s[t][0] = s[t][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ds = 0; ds < NDS; ++ds)
 #pragma unroll
@@ -763,20 +772,20 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
                 const int row = 16 * kt + c, swz = CPR == 16 ? row & 15 : (row >> 1) & 7;
                 const Frag<T> kf = Frag<T>::load(reinterpret_cast<const T*>(sk + (row * CPR + ((ds * 4 + g) ^ swz)) * 16));
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
+                for (int t = 0; t < RT; ++t) {
                     mma(s[t][kt], kf, qh[t][ds]);
                     mma(s[t][kt], kf, ql[t][ds]);
                 }
             }
         // s[t][kt][r] = S^T[key = 32 blk + 16kt + 4g + r][row w0 + 16t + c]
         const bool whole = 32 * blk + 31 <= L + w0;   // every key is visible to every row of the wave
-        Frag<T> ph[2], pl[2];
-        float alpha[2];
+        Frag<T> ph[RT], pl[RT];
+        float alpha[RT];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int t = 0; t < RT; ++t) {
             float sv8[8], p[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sv8[e] = s[t][e / 4][e % 4] * a.scale;
+            for (int e = 0; e < 8; ++e) sv8[e] = s[t][e / 4][e % 4];
             if (!whole) {
                 const int m = w0 + 16 * t + c;
 #pragma unroll
@@ -786,7 +795,7 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
                 }
             }
             float bm = fmaxf(fmaxf(fmaxf(sv8[0], sv8[1]), fmaxf(sv8[2], sv8[3])),
-                             fmaxf(fmaxf(sv8[4], sv8[5]), fmaxf(sv8[6], sv8[7])));
+                             fmaxf(fmaxf(sv8[4], sv8[5]), fmaxf(sv8[6], sv8[7]))) * a.scale;   // scale > 0
             bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
             bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
             const float nmax = fmaxf(rmax[t], bm);
@@ -795,10 +804,10 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
             float ps = 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                p[e] = expf(sv8[e] - base);
+                p[e] = expf(fmaf(sv8[e], a.scale, -base));
                 ps += p[e];
             }
-            rsum[t] = rsum[t] * alpha[t] + ps;
+            rsum[t] = fmaf(rsum[t], alpha[t], ps);
             rmax[t] = nmax;
             split_frag<T>(p, ph[t], pl[t]);
         }
@@ -806,7 +815,7 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
         for (int dt = 0; dt < NDT; ++dt) {
             const Frag<T> vf = Frag<T>::load(reinterpret_cast<const T*>(sv + (16 * dt + c) * 64 + g * 16));
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < RT; ++t) {
                 o[t][dt] *= alpha[t];
                 mma(o[t][dt], vf, ph[t]);
                 mma(o[t][dt], vf, pl[t]);
@@ -815,17 +824,17 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
     }
     __syncthreads();   // the stage buffers are free
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < RT; ++t) {
         rsum[t] += __shfl_xor(rsum[t], 16, 64);
         rsum[t] += __shfl_xor(rsum[t], 32, 64);
     }
     // the output tiles are shared out over the parities: wave kp merges tiles kp * OWN .. and leaves its
     // partials of the others, [rs][t][dt][NKP - 1 others], and its row maxima and sums, [rs][t][kp]
     constexpr int OWN = NDT / NKP;
-    f32x4_t* mo = reinterpret_cast<f32x4_t*>(smem) + rs * 2 * NDT * (NKP - 1) * 64 + lane;
-    float* ms = reinterpret_cast<float*>(smem + 4 * NDT * (NKP - 1) * 1024) + rs * 2 * NKP * 128 + lane;
+    f32x4_t* mo = reinterpret_cast<f32x4_t*>(smem) + rs * RT * NDT * (NKP - 1) * 64 + lane;
+    float* ms = reinterpret_cast<float*>(smem + 4 * NDT * (NKP - 1) * 1024) + rs * RT * NKP * 128 + lane;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < RT; ++t) {
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
             const int own = dt / OWN;
@@ -836,7 +845,7 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
     }
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < RT; ++t) {
         const int m = w0 + 16 * t + c;
         float w[NKP], gmax = -INFINITY, den = 0.f;
 #pragma unroll
@@ -846,9 +855,9 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
         }
         if (m >= q) continue;   // its rows saw no key
 #pragma unroll
-        for (int k = 0; k < NKP; ++k) {
+        for (int k = NKP - 1; k >= 0; --k) {
             w[k] = w[k] == -INFINITY ? 0.f : expf(w[k] - gmax);
-            den += w[k] * ms[(t * NKP + k) * 128 + 64];
+            den = fmaf(w[k], ms[(t * NKP + k) * 128 + 64], den);
         }
         const float inv = 1.0f / den;
 #pragma unroll
@@ -857,8 +866,11 @@ __global__ void __launch_bounds__(128 * NKP, 2) attn_tiles_kernel(AttnArgs a) {
             if (own != kp) continue;
             f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int k = 0; k < NKP; ++k)
-                acc += (k == own ? o[t][dt] : mo[((t * NDT + dt) * (NKP - 1) + (k < own ? k : k - 1)) * 64]) * w[k];
+            for (int k = NKP - 1; k >= 0; --k) {
+                const f32x4_t ov = k == own ? o[t][dt] : mo[((t * NDT + dt) * (NKP - 1) + (k < own ? k : k - 1)) * 64];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[r] = fmaf(ov[r], w[k], acc[r]);
+            }
             store_out<T, DH>(a, b, h, m, 16 * dt + 4 * g, acc * inv);
         }
     }
@@ -874,11 +886,11 @@ hipError_t launch_attention_rows(int dtype, int head_dim, const AttnArgs& a, hip
     int threads = 64 * kRowWaves;
     const int tiles = a.B * a.H * ((a.q + 63) / 64);
     if (dtype == 1) {
-        // at most one workgroup per compute unit: 8 waves, half the steps; else two of 4 waves share it, one's
-        // start and merge beside the other's steps
+        // at most one workgroup per compute unit: 8 waves of one row tile; else two of 4 waves and two row tiles
+        // share it, one's start and merge beside the other's steps
         const bool wide = tiles <= 256;
-        if (head_dim == 128) kern = wide ? attn_tiles_kernel<128, 4> : attn_tiles_kernel<128, 2>;
-        else if (head_dim == 64) kern = wide ? attn_tiles_kernel<64, 4> : attn_tiles_kernel<64, 2>;
+        if (head_dim == 128) kern = wide ? attn_tiles_kernel<128, 1> : attn_tiles_kernel<128, 2>;
+        else if (head_dim == 64) kern = wide ? attn_tiles_kernel<64, 1> : attn_tiles_kernel<64, 2>;
         threads = wide ? 512 : 256;
     }
     else if (head_dim == 64) kern = attn_rows_kernel<float, 64>;

@@ -1,5 +1,6 @@
-"""Rows of a large block (more than 64 rows), bit for bit: layer 0's normalised rows against the kernels of decode
-blocks, and RoPE's rounding.  A token enters layer 0 the same whether it comes in a prompt or in a draft block."""
+"""Rows of a large block (more than 64 rows) against the kernels of decode blocks, bit for bit: layer 0's
+normalised rows, RoPE's rounding, and attention rows whose keys lie in one 32-key block.  A token then enters
+layer 0 the same whether it comes in a prompt or in a draft block."""
 import ctypes
 
 import numpy as np
@@ -7,6 +8,7 @@ import pytest
 import torch
 
 from paper_2403_18647_amd import binding as B
+from paper_2403_18647_amd import synth
 from test_gpu_prefill_mma import QKV, STORE, _base, _frag, _launch, _operands
 
 pytestmark = pytest.mark.gpu
@@ -93,3 +95,26 @@ def test_rope_rounding(cfg):
 
     assert torch.equal(qb.cpu(), rot(v[:, 0]))
     assert torch.equal(kc[:, :m].cpu(), rot(v[:, 1]).transpose(0, 1).bfloat16())
+
+
+@pytest.mark.parametrize("dh,heads,batch", [(128, 2, 1), (64, 4, 1), (128, 2, 65), (64, 2, 65)])   # both workgroup sizes
+def test_attention_one_key_block(dh, heads, batch):
+    sh = synth.small_shape(n_layers=1, d_model=heads * dh, n_heads=heads, head_dim=dh, d_ffn=64, vocab=64, dtype="bf16")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(dh)
+    w = [torch.zeros(synth.tensor_shape(sh, n), device="cuda", dtype=torch.float32 if synth.is_gain(n) else torch.bfloat16)
+         for n in synth.tensor_names(sh)]
+    kv = [torch.randn((batch, 96, heads, dh), generator=g, device="cuda") for _ in range(2)]
+    pos = torch.arange(96, dtype=torch.int32, device="cuda").repeat(batch)
+    qs = torch.randn((batch, 65, heads * dh), generator=g, device="cuda") * 2
+    outs = []
+    for q in (65, 26):
+        ctx = B.Context(B.make_config(sh, batch, 96, 65), w)
+        B.sdsat_kv_write(ctx.handle, 0, batch, 96, *kv, pos)
+        B.sdsat_set_cache_len(ctx.handle, [5] * batch)
+        out = torch.empty((batch, q, heads * dh), device="cuda")
+        B.sdsat_attention(ctx.handle, 0, batch, q, qs[:, :q].contiguous(), None, out)
+        torch.cuda.synchronize()
+        outs.append(out[:, :26])
+        ctx.close()
+    assert torch.equal(*outs)
