@@ -208,6 +208,15 @@ hipError_t launch_embed_norm_rows(int dtype, const void* embed, int n_rows_emb, 
 // best [B*q] and counter [B]: zero between launches
 hipError_t launch_verify_greedy(const float* logits, int B, int q, int V, const int* drafts, int drafts_ld,
                                 int* tokens_out, int* n_accept, unsigned long long* best, int* counter, hipStream_t s);
+// The gathered sampler reads its row, tile by tile of kNucleusThreads ids, through a buffer resource of V floats:
+// id tile * kNucleusThreads + t at vector offset `voff`, scalar offset `soff` (bytes).  The bounds check compares the
+// vector offset with the resource's size and does not cover the scalar one, so the whole offset is in the former:
+// ids past V then read zeros without a memory access.
+constexpr int kNucleusThreads = 1024;
+struct BufOffset { uint32_t voff, soff; };
+__host__ __device__ inline BufOffset nucleus_read(int tile, int t) {
+    return {(uint32_t)(tile * kNucleusThreads + t) * 4u, 0u};
+}
 // row_depth (optional, a draft tree; drafts must be NULL): every row is sampled with the uniform of
 // position pos0[b] + row_depth[b*q + row]
 hipError_t launch_verify_nucleus(const float* logits, int B, int q, int V, const int* drafts, int drafts_ld,

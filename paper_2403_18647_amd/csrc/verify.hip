@@ -202,7 +202,7 @@ hipError_t launch_verify_greedy(const float* logits, int B, int q, int V, const 
 // 1024 threads x 32 contiguous ids (V <= 32768); each thread keeps its ids' keys and float64
 // weights in registers and a bit mask (one bit per id) of the kept and nucleus ids.  Longer
 // vocabularies go chunk by chunk (sample_row_chunked).
-static constexpr int kNT = 1024;
+static constexpr int kNT = kNucleusThreads;
 static constexpr int kCPT = 32;
 using Bits = uint32_t;
 static_assert(kCPT <= 32, "one mask bit per id");
@@ -748,8 +748,10 @@ __device__ __forceinline__ bool sample_row_few(const float* row, int V, double T
     const __amdgpu_buffer_rsrc_t rs = buf_rsrc(row, (uint32_t)V * 4);   // reads past V are not made
     float v[kCPT];
 #pragma unroll
-    for (int i = 0; i < kCPT; ++i)
-        v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, t * 4, i * (kNT * 4), 0));
+    for (int i = 0; i < kCPT; ++i) {
+        const BufOffset o = nucleus_read(i, t);
+        v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, o.voff, o.soff, 0));
+    }
     uint32_t kmax = 0;
 #pragma unroll
     for (int i = 0; i < kCPT; ++i) {

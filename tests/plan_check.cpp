@@ -17,6 +17,8 @@
 //     not whole heads, rows not whole sequences, caches not in 32-key blocks, missing buffers; the
 //     prefill attention with a tree mask or a head width it has no instance for.  Only invalid
 //     argument sets are passed (a valid one would launch).
+//  6. The gathered nucleus sampler's reads: inside the row, or past its end by the vector offset alone
+//     (the part of a buffer access that the bounds check covers).
 #include <algorithm>
 #include <cstdio>
 #include <vector>
@@ -176,6 +178,17 @@ int main() {
             for (int dtype : {0, 1})
                 CHECK(launch_attention_rows(dtype, b.head_dim, b.a, nullptr) == hipErrorInvalidValue,
                       "prefill attention accepted: %s", b.what);
+    }
+    for (int V : {1, 3, 1000, 1023, 1024, 1025, 8193, 31744, 32016, 32768}) {
+        long out = 0;
+        for (int tile = 0; tile < 32; ++tile)
+            for (int t = 0; t < kNucleusThreads; ++t) {
+                const BufOffset o = nucleus_read(tile, t);
+                const long id = (long)tile * kNucleusThreads + t;
+                const bool in = o.voff + o.soff + 4 <= 4u * V;
+                out += o.voff + o.soff != 4u * id || in != (id < V) || (!in && o.voff < 4u * V);
+            }
+        CHECK(out == 0, "nucleus reads of a row of %d ids: %ld unbounded", V, out);
     }
     std::printf("%s (%d failed)\n", failures ? "FAILED" : "ok", failures);
     return failures ? 1 : 0;
