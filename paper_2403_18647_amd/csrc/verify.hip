@@ -485,7 +485,7 @@ __device__ __forceinline__ uint32_t radix_refine(const uint32_t (&keys)[N], Bits
 #pragma unroll
         for (int i = 0; i < N; ++i) cnt += ((kept >> i) & 1u) && (keys[i] & in) == prefix;
         int slot = block_exscan_total_i(cnt, s_i, &total);
-        if (total > 64) continue;
+        if (total > 64 || total == 0) continue;   // 0: rounding left every sum short and no id holds the lowest digit
         double* s_w = hist;                                      // [64] weights
         uint32_t* s_k = reinterpret_cast<uint32_t*>(hist + 64);   // [64] keys
         if (cnt) {
@@ -692,7 +692,8 @@ __device__ __forceinline__ double exp_neg(double x) {
 }
 
 // x / T with r = 1 / T: one Newton step on the product gives the correctly rounded quotient (Markstein),
-// in 3 operations for the division's dozen; infinities (ids past V) keep the product.
+// in 3 operations for the division's dozen; infinities (ids past V) keep the product.  T finite: an infinite
+// one gives NaN where the division gives 0.
 __device__ __forceinline__ double div_by(double x, double T, double r) {
     const double q = x * r;
     return __builtin_isfinite(q) ? fma(fma(-q, T, x), r, q) : q;
@@ -740,7 +741,7 @@ __device__ __forceinline__ int finish_row(const uint32_t (&keys)[N], const doubl
 // The others are gathered in id order, kFew to a thread, and digits in which the range's ends agree need no
 // pass.  sample_row below keeps 32 ids per thread through every step; its code, unrolled for that, is
 // fetched once per launch and took most of its 66 us.  4 x 6 rows of 32016 ids: 66.1 -> 42.6 us.
-// Returns false (nothing decided) when too many ids are left.
+// Returns false (nothing decided) when too many ids are left or the total mass is not finite.
 __device__ __forceinline__ bool sample_row_few(const float* row, int V, double T, double p, double u, double* s_hist,
                                                double* s_tot, double* s_d, int* s_i, float* s_f, int* out) {
     __shared__ int s_cnt[kCPT * kWaves];
@@ -772,6 +773,8 @@ __device__ __forceinline__ bool sample_row_few(const float* row, int V, double T
         if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // 32 exponentials interleaved would spill
     }
     block_sum_d<2>(tot, s_d);
+    // a NaN or infinite logit, a row of -inf, an infinite T: no threshold to find here (the division below serves T = inf)
+    if (!__builtin_isfinite(tot[0])) return false;
     const double pE = p * tot[0];
     const uint32_t kl = tot[1] <= (1.0 - p) * tot[0] * (1.0 - 1e-9)
                             ? k9 : order_key((float)((double)lmax + T * (log((1.0 - p) / V) - 1.0)));

@@ -39,3 +39,52 @@ def test_few(vocab, temp, p):
             # a draw this close to a decision boundary may go either way with float64 sums in another order
             assert int(got[j]) == int(want) or margin < 1e-9, (vocab, temp, p, seed, j)
     ctx.close()
+
+
+def _verify(lg, temp, p, seed):
+    q, vocab = lg.shape
+    sh = synth.small_shape(n_layers=1, vocab=vocab)
+    w = [torch.zeros(synth.tensor_shape(sh, n), device="cuda") for n in synth.tensor_names(sh)]
+    ctx = B.Context(B.make_config(sh, 1, 64, q), w)
+    pos0 = torch.tensor([17], dtype=torch.int32, device="cuda")
+    drafts = torch.zeros((1, q - 1), dtype=torch.int32, device="cuda")
+    tok = torch.empty((1, q), dtype=torch.int32, device="cuda")
+    acc = torch.empty(1, dtype=torch.int32, device="cuda")
+    B.sdsat_verify_nucleus(ctx.handle, 1, q, torch.from_numpy(lg).cuda(), drafts, temp, p, 0, seed, pos0, tok, acc)
+    torch.cuda.synchronize()
+    ctx.close()
+    return tok.cpu().numpy()[0]
+
+
+@pytest.mark.parametrize("vocab", [3, 1000, 8192, 8193, 32016, 32768])
+@pytest.mark.parametrize("p", [0.5, 0.95])
+def test_infinite_temperature(vocab, p):
+    """Every weight is 1: the nucleus is the p V largest logits (ties at the threshold kept), drawn uniformly."""
+    rng = np.random.default_rng(vocab)
+    lg = rng.standard_normal((4, vocab)).astype(np.float32) * 4
+    lg[1] = np.round(lg[1])
+    got = _verify(lg, float("inf"), p, 5)
+    for j in range(4):
+        srt = np.sort(lg[j])[::-1]
+        n = int(np.ceil(float(np.float32(p)) * vocab))   # whole sums: the threshold is exact
+        ids = np.nonzero(lg[j] >= srt[n - 1])[0]
+        assert got[j] == ids[int(S.uniform(5, 0, 17 + j) * len(ids))], (vocab, p, j)
+
+
+@pytest.mark.parametrize("vocab", [3, 1000, 8192, 8193, 32016, 32768])
+def test_no_finite_mass(vocab):
+    """Rows whose mass is no number have no threshold: the last id, never one outside the vocabulary."""
+    rng = np.random.default_rng(vocab)
+    lg = rng.standard_normal((6, vocab)).astype(np.float32) * 4
+    lg[0, 0] = np.nan
+    lg[1, vocab // 2] = -np.float32(np.nan)
+    lg[2, vocab - 1] = np.inf
+    lg[3] = -np.inf
+    lg[4] = np.nan
+    lg[5, 1] = np.inf
+    lg[5, 2] = np.inf
+    for temp, p in ((0.8, 0.95), (float("inf"), 0.5)):
+        got = _verify(lg, temp, p, 3)
+        if temp < np.inf:
+            assert (got == vocab - 1).all(), got
+        assert ((got >= 0) & (got < vocab)).all(), got
