@@ -148,7 +148,15 @@ GemmPlan plan_gemm_resid(int M, int n_tiles, int k_steps) {
         p.lds_bytes = 0;   // partial tiles go to memory
         return p;
     }
-    if (p.ntw != 1 || n_tiles <= 256 || n_tiles > 512 || k_steps < 256) return p;   // the row kernel: 8192 columns
+    if (n_tiles > 512) {   // whole: the row kernel behind a split takes 8192 columns.  One tile per workgroup as for the
+                           // narrow ones (9216 wide, FFN 24576, one layer, 24 / 48 / 64 rows: 458 / 569 / 643 us;
+                           // 2 tiles at 24 rows and 4 beyond, row-major rows: 580 / 630 / 776 us)
+        p.ntw = 1;
+        p.grid = n_tiles;
+        p.lds_bytes = p.waves * p.mt * 64 * 16;
+        return p;
+    }
+    if (n_tiles <= 256 || k_steps < 256) return p;
     auto spread = [&](int k) {   // workgroup rounds over the average, per compute unit
         const long n = (long)n_tiles * k;
         return (double)((n + 255) / 256) * 256.0 / (double)n;
@@ -521,7 +529,7 @@ __global__ void __launch_bounds__(NTW > 1 ? 256 : 512) gemm_kernel(GemmArgs a) {
 template <typename T, int EP, bool XF>
 static hipError_t launch_mt(const GemmPlan& p, const GemmArgs& a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     const dim3 grid(p.grid), block(64 * p.waves);
-    if (p.waves > (p.ntw > 1 ? 4 : 8)) return hipErrorInvalidValue;
+    if (p.waves > (p.ntw > 1 ? 4 : 8) || !gemm_instance(EP, p.mt, p.ntw, XF)) return hipErrorInvalidValue;
     const bool split = p.ksplit > 1;   // ev1 is then the row kernel's
     if (split && (EP != EP_RESID || !a.part || a.ksplit != p.ksplit ||
                   p.grid != (a.n_tiles + p.ntw - 1) / p.ntw * p.ksplit))
@@ -531,7 +539,6 @@ static hipError_t launch_mt(const GemmPlan& p, const GemmArgs& a, hipStream_t s,
         if (ev0) hipExtLaunchKernelGGL(kernel, grid, block, p.lds_bytes, s, ev0, split ? nullptr : ev1, 0, a);
         else hipLaunchKernelGGL(kernel, grid, block, p.lds_bytes, s, a);
     };
-    // several row tiles: element-type rows only; several column tiles: 3, or 4 of a split residual GEMM
     constexpr int NW = EP == EP_RESID ? 4 : 3;
     if (p.mt == 1 && p.ntw == 1) go(gemm_kernel<T, EP, 1, 1, XF>);
     else if constexpr (!XF) {

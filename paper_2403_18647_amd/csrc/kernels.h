@@ -83,6 +83,12 @@ GemmPlan plan_gemm(int M, int n_tiles, int k_steps);
 // The residual GEMMs' plan with each tile's waves spread over ksplit workgroups where that balances
 // the compute units (same wave slices, same fold order: the same values).
 GemmPlan plan_gemm_resid(int M, int n_tiles, int k_steps);
+// The kernel instances: one column tile per workgroup with any rows (float rows, xf: one row tile), or several
+// row tiles of element rows with 3 column tiles, 4 for the split residual GEMM.  Every plan has one.
+inline bool gemm_instance(int ep, int mt, int ntw, bool xf) {
+    if (mt < 1 || mt > 4 || (xf && (mt > 1 || ep == EP_RESID))) return false;
+    return ntw == 1 || (mt > 1 && ntw == (ep == EP_RESID ? 4 : 3));
+}
 // bytes of the partial-tile buffer the residual GEMMs of this shape need (0: never split)
 size_t gemm_resid_part_bytes(int n_tiles, int k_steps, int max_rows);
 // ev0 / ev1 (optional): events taken at the kernel's own start and end (its

@@ -12,6 +12,8 @@
 //     up to 64 rows.
 //  4. Skinny GEMMs: the contraction slices (waves x workgroups per tile) do not depend on the rows
 //     M, for M = 1..64, so a row's value is the same in any block.
+//     Every plan of 1..64 rows, for matrices of up to 1024 column tiles, has a kernel instance, and what
+//     a split leaves to the row kernel behind it fits that kernel (parts, 8192 columns).
 //  5. The prefill launches refuse, before any device call, arguments their kernels do not handle:
 //     fused epilogues with a split contraction, heads other than 64 / 128 columns, segments that are
 //     not whole heads, rows not whole sequences, caches not in 32-key blocks, missing buffers; the
@@ -95,6 +97,20 @@ int main() {
             }
         }
     }
+    for (int n_tiles = 1; n_tiles <= 1024; ++n_tiles)
+        for (int k_steps : {1, 2, 8, 31, 64, 128, 255, 256, 260, 432, 688, 1024})
+            for (int M = 1; M <= 64; ++M) {
+                const GemmPlan p = plan_gemm(M, n_tiles, k_steps), r = plan_gemm_resid(M, n_tiles, k_steps);
+                CHECK(gemm_instance(EP_STORE, p.mt, p.ntw, false) && gemm_instance(EP_QKV, p.mt, p.ntw, M <= 16) &&
+                          gemm_instance(EP_SWIGLU, p.mt, p.ntw, M <= 16) && p.ksplit == 1 && p.waves <= (p.ntw > 1 ? 4 : 8),
+                      "no instance: tiles %d steps %d M %d ntw %d waves %d", n_tiles, k_steps, M, p.ntw, p.waves);
+                CHECK(gemm_instance(EP_RESID, r.mt, r.ntw, false) && r.waves <= (r.ntw > 1 ? 4 : 8) &&
+                          (r.ntw == 1 || r.ksplit > 1) && r.grid == (n_tiles + r.ntw - 1) / r.ntw * r.ksplit &&
+                          (r.ksplit == 1 ? r.lds_bytes == r.waves * r.mt * r.ntw * 1024
+                                         : r.waves * r.ksplit <= kFoldMaxParts && n_tiles <= 512),
+                      "residual plan: tiles %d steps %d M %d ntw %d waves %d split %d", n_tiles, k_steps, M, r.ntw,
+                      r.waves, r.ksplit);
+            }
     // 5. launch-argument checks (each set below is invalid in exactly the way its label says)
     {
         int dummy[64];

@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2403_18647_amd import binding as B
+from paper_2403_18647_amd import synth
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +33,25 @@ def test_three_tiles(m, n, k):
     assert ((y.double() - xb @ w.double().t()).abs() <= bound).all()
     for r in (0, 16, m - 1):
         assert torch.equal(_linear(1, n, k, x[r:r + 1].contiguous(), packed)[0], y[r]), r
+
+
+@pytest.mark.parametrize("batch", [3, 5, 8])   # 2, 3 and 4 row tiles
+def test_residual_beyond_512_tiles(batch):
+    """d_model > 8192: the O and down GEMMs of blocks of 17 to 64 rows, whole (not split), give each sequence the
+    values of its own 8-row block."""
+    sh = synth.small_shape(n_layers=1, d_model=8320, n_heads=65, head_dim=128, d_ffn=256, vocab=64, dtype="bf16")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(batch)
+    w = [1 + 0.1 * torch.randn(synth.tensor_shape(sh, n), generator=g, device="cuda") if synth.is_gain(n) else
+         0.02 * torch.randn(synth.tensor_shape(sh, n), generator=g, device="cuda", dtype=torch.bfloat16)
+         for n in synth.tensor_names(sh)]
+    tok = torch.randint(0, 64, (batch, 8), generator=g, device="cuda", dtype=torch.int32)
+    ctx = B.Context(B.make_config(sh, batch, 32, 8), w)
+    out = torch.empty((batch, 8, 64), device="cuda")
+    one = torch.empty_like(out)
+    B.sdsat_forward_block(ctx.handle, batch, 8, tok, None, out)
+    for b in range(batch):
+        B.sdsat_forward_block(ctx.handle, 1, 8, tok[b:b + 1].contiguous(), None, one[b])
+    torch.cuda.synchronize()
+    ctx.close()
+    assert torch.equal(out, one)
