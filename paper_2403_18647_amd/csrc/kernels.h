@@ -186,6 +186,10 @@ struct PrefillGemmArgs {
 };
 constexpr int kPrefillMaxSplit = 4;
 int prefill_gemm_ksplit(int M, int N, int K);
+// bf16: 32-wide steps of one part of a split contraction (whole pairs; the last part takes the rest)
+__host__ __device__ inline int prefill_mma_part(int k_steps, int ksplit) {
+    return ((k_steps + 1) / 2 + ksplit - 1) / ksplit * 2;
+}
 // bf16: the workgroup tile (an index into the kernel's instances) a product of this shape takes
 int plan_prefill_mma(int M, int n_tiles, int k_steps, int ksplit);
 int prefill_mma_configs();

@@ -357,8 +357,8 @@ __global__ void __launch_bounds__(64 * WM * WN, WM * WN >= 8 || NST * (WM * TM +
     const int grp = t / (8 * n_tiles), in = t - grp * 8 * n_tiles, gm = min(8, m_tiles - 8 * grp);
     const int mt0 = (8 * grp + in % gm) * BMT, nt0 = in / gm * BNT;
 
-    const int per = ((p.k_steps + 1) / 2 + p.ksplit - 1) / p.ksplit * 2, k0 = kpart * per;   // whole 64-column pairs
-    const int steps = min(p.k_steps, k0 + per) - k0;
+    const int per = prefill_mma_part(p.k_steps, p.ksplit), k0 = kpart * per;
+    const int steps = min(p.k_steps, k0 + per) - k0;   // at least 1: launch_prefill_mma
 
     // this wave's fragments of a stage (where they do not divide, the last is repeated: the same bytes to
     // the same place); tiles past the end read the last one and are not stored
@@ -649,7 +649,7 @@ int plan_prefill_mma(int M, int n_tiles, int k_steps, int ksplit) {
 
 hipError_t launch_prefill_mma(int cfg, const PrefillGemmArgs& p, hipStream_t s) {
     if (!p.A || !p.Wp || p.n_tiles < (p.N + 15) / 16 || p.k_steps < (p.K + 31) / 32 || p.lda != 32 * p.k_steps ||
-        p.ksplit > p.k_steps)
+        p.ksplit < 1 || (p.ksplit - 1) * prefill_mma_part(p.k_steps, p.ksplit) >= p.k_steps)   // no empty part
         return hipErrorInvalidValue;
     switch (cfg) {
         case 0: return go_mma<2, 4, 8, 4, 4>(p, s);

@@ -166,6 +166,23 @@ int main() {
             CHECK(k == t.parts && k >= 1 && k <= kPrefillMaxSplit, "prefill split of %d x %d x %d: %d parts, expected %d",
                   t.M, t.N, t.K, k, t.parts);
         }
+        // bf16: a split that would leave a part without a step is refused; the planned ones leave none
+        for (auto t : {std::make_pair(5, 4), std::make_pair(3, 2), std::make_pair(1, 2), std::make_pair(2, 4)}) {
+            if ((t.second - 1) * prefill_mma_part(t.first, t.second) < t.first) continue;   // valid: it would launch
+            PrefillGemmArgs p{};
+            p.M = 140; p.N = p.n_per = 256; p.K = p.lda = 32 * t.first; p.A = p.W0 = p.Wp = ptr; p.n_tiles = 16;
+            p.k_steps = t.first; p.ksplit = t.second; p.ep = PG_STORE; p.C = reinterpret_cast<float*>(ptr); p.ldc = 256;
+            p.c_part = (size_t)p.M * p.ldc;
+            for (int cfg = 0; cfg < prefill_mma_configs(); ++cfg)
+                CHECK(launch_prefill_mma(cfg, p, nullptr) == hipErrorInvalidValue, "prefill GEMM accepted %d parts of %d steps",
+                      t.second, t.first);
+        }
+        for (int K = 8; K <= 65536; K += 8)
+            for (int M : {65, 140, 511, 1023, 4092})
+                for (int N : {64, 1024, 4096}) {
+                    const int parts = prefill_gemm_ksplit(M, N, K), steps = (K + 31) / 32;
+                    CHECK((parts - 1) * prefill_mma_part(steps, parts) < steps, "empty part: M %d N %d K %d", M, N, K);
+                }
         for (int parts : {0, kPrefillMaxSplit + 1})
             CHECK(launch_resid_norm_rows(1, reinterpret_cast<const float*>(ptr), parts, 0, 256, 4, 256,
                                          reinterpret_cast<float*>(ptr), 256, reinterpret_cast<const float*>(ptr), 1e-5f,
