@@ -121,12 +121,14 @@ int main() {
             p.ksplit = 1; p.ep = PG_QKV; p.q = 70; p.H = 2; p.Dh = 128; p.S_max = 512;
             p.cache_len = dummy; p.rope = reinterpret_cast<const float*>(ptr); p.qbuf = reinterpret_cast<float*>(ptr);
             p.kc = p.vc = ptr; p.err = dummy;
+            p.Wp = ptr; p.n_tiles = 48; p.k_steps = 8;
             return p;
         };
         auto swiglu = [&]() {
             PrefillGemmArgs p{};
             p.M = 140; p.N = 2 * 688; p.K = 256; p.A = ptr; p.lda = 256; p.W0 = p.W1 = ptr; p.n_per = 688;
-            p.ksplit = 1; p.ep = PG_SWIGLU; p.u = ptr; p.ldu = 688;
+            p.ksplit = 1; p.ep = PG_SWIGLU; p.u = ptr; p.ldu = 704;
+            p.Wp = ptr; p.n_tiles = 86; p.k_steps = 8;
             return p;
         };
         struct Bad { const char* what; PrefillGemmArgs p; };
@@ -144,11 +146,13 @@ int main() {
         { auto p = swiglu(); p.u = nullptr; bad.push_back({"SwiGLU without an output", p}); }
         { auto p = swiglu(); p.ldu = 600; bad.push_back({"SwiGLU output rows too short", p}); }
         { auto p = swiglu(); p.ksplit = 2; bad.push_back({"SwiGLU epilogue with a split contraction", p}); }
-        { auto p = swiglu(); p.N = 3 * 688; p.W2 = ptr; bad.push_back({"SwiGLU with three segments", p}); }
-        { auto p = swiglu(); p.ep = PG_STORE; bad.push_back({"plain store without C", p}); }
+        { auto p = swiglu(); p.N = 3 * 688; p.W2 = ptr; p.n_tiles = 129; bad.push_back({"SwiGLU with three segments", p}); }
+        { auto p = swiglu(); p.ep = PG_STORE; p.ldc = p.N; bad.push_back({"plain store without C", p}); }
+        { auto p = swiglu(); p.K = 264; bad.push_back({"rows shorter than the contraction", p}); }
         { auto p = swiglu(); p.ep = PG_STORE; p.C = reinterpret_cast<float*>(ptr); p.ldc = 100;
           bad.push_back({"plain store with C rows too short", p}); }
         { auto p = swiglu(); p.ep = PG_STORE; p.C = reinterpret_cast<float*>(ptr); p.ldc = p.N; p.ksplit = 5;
+          p.K = p.lda = 1280; p.k_steps = 40;   // 5 parts of 8 steps
           p.c_part = (size_t)p.M * p.ldc; bad.push_back({"split into more parts than the partial buffers hold", p}); }
         { auto p = swiglu(); p.ep = PG_STORE; p.C = reinterpret_cast<float*>(ptr); p.ldc = p.N; p.ksplit = 4;
           p.c_part = (size_t)p.M * p.ldc - 1; bad.push_back({"split partials that overlap", p}); }
@@ -156,6 +160,19 @@ int main() {
             for (int dtype : {0, 1})
                 CHECK(launch_prefill_gemm(dtype, b.p, nullptr) == hipErrorInvalidValue, "prefill GEMM accepted: %s",
                       b.what);
+        // bf16 only: the packed matrix
+        std::vector<Bad> bad16;
+        { auto p = swiglu(); p.Wp = nullptr; bad16.push_back({"no packed matrix", p}); }
+        { auto p = swiglu(); p.n_tiles = 85; bad16.push_back({"fewer column tiles than columns", p}); }
+        { auto p = swiglu(); p.lda = 288; bad16.push_back({"row stride not that of the packed steps", p}); }
+        { auto p = swiglu(); p.k_steps = 9; bad16.push_back({"more steps than the row stride", p}); }
+        for (const Bad& b : bad16)
+            CHECK(launch_prefill_gemm(1, b.p, nullptr) == hipErrorInvalidValue, "prefill GEMM (bf16) accepted: %s", b.what);
+        {
+            auto p = swiglu();
+            p.K = 264;
+            CHECK(launch_prefill_mma(0, p, nullptr) == hipErrorInvalidValue, "prefill GEMM (bf16) accepted: fewer steps than the contraction");
+        }
         // split plans: O and down of a 511-row 7B block fill two workgroups per compute unit; a block of
         // 256 tiles or a short contraction stays whole; the partial buffers hold every plan
         struct Split { int M, N, K, parts; };
