@@ -17,6 +17,7 @@
 // block-wide prefix scan in id order.  All sums use a fixed reduction order,
 // so results are reproducible run to run.
 #include <algorithm>
+#include <cmath>
 
 #include "device.h"
 #include "kernels.h"
@@ -733,17 +734,45 @@ __device__ __forceinline__ int finish_row(const uint32_t (&keys)[N], const doubl
 
 // Top-p without top-k, the usual case: only the ids that can be in the nucleus are kept.  Consecutive threads
 // hold consecutive ids (32 tiles of 1024); the total mass takes every id, and
-//  * the ids below lmax - 9 T, where they hold at most (1 - p) of the mass, or
-//  * those below lmax + T (ln((1 - p) / V) - 1) otherwise (the ids at or below the threshold hold at least
+//  * the ids below lmax - T (6 - ln(1 - p)) (9 T at p 0.95), where they hold at most (1 - p) of the mass, or
+//  * those below lmax - T (1 - ln((1 - p) / V)) otherwise (the ids at or below the threshold hold at least
 //    (1 - p) E >= 1 - p, none more than the threshold's own weight, so that weight is at least (1 - p) / V;
 //    the 1 is for rounding)
 // neither move the threshold nor are in the nucleus (std-4 logits, T 0.8, p 0.95: 1000 of 32016 are left).
 // The others are gathered in id order, kFew to a thread, and digits in which the range's ends agree need no
 // pass.  sample_row below keeps 32 ids per thread through every step; its code, unrolled for that, is
-// fetched once per launch and took most of its 66 us.  4 x 6 rows of 32016 ids: 66.1 -> 42.6 us.
+// fetched once per launch and took most of its 66 us.  4 x 6 rows of 32016 ids: 66.5 -> 43.8 us.
+// Flat rows leave more than kNT kFew ids (std 1.3, T 0.8, p 0.95: 29000 of 32016; their nucleus alone is 16000)
+// and go to sample_row.  That is seen before the float64 exponentials are paid for: the ids above the first cut
+// are counted and placed first, and where they are many a float32 sum says whether that cut will hold.  The row
+// waits in s_hist for sample_row, whose own load, 128 bytes apart per lane, costs more than this one.  4 x 6
+// rows of std 1.3 / 2 / 3 / 4: 71.0 / 71.3 / 49.2 / 43.8 us (with the exponentials before the count 89.1 / 88.5 /
+// 45.9 / 42.8, by sample_row alone 68.9 / 68.1 / 68.2 / 66.5).
 // Returns false (nothing decided) when too many ids are left or the total mass is not finite.
-__device__ __forceinline__ bool sample_row_few(const float* row, int V, double T, double p, double u, double* s_hist,
-                                               double* s_tot, double* s_d, int* s_i, float* s_f, int* out) {
+struct NucleusCuts { double first, second; };   // in units of T below the largest logit
+static NucleusCuts nucleus_cuts(float top_p, int V) {
+    const double rest = 1.0 - std::min((double)top_p, 1.0);
+    return {6.0 - std::log(rest), 1.0 - std::log(rest / V)};
+}
+
+__device__ __forceinline__ int row_slot(int id) {   // runs of 32 ids, a thread's of sample_row; quads permuted by run against bank conflicts
+    return (id & ~28) | ((((id >> 2) ^ (id >> 5)) & 7) << 2);
+}
+
+// ids id0 .. id0+31 of the row that sample_row_few left in s_hist, as order-preserving keys
+__device__ __forceinline__ void row_keys(const double* s_hist, int id0, uint32_t (&keys)[kCPT]) {
+    const float* s_row = reinterpret_cast<const float*>(s_hist);
+#pragma unroll
+    for (int i = 0; i < kCPT; i += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(s_row + row_slot(id0 + i));
+        keys[i] = order_key(x.x); keys[i + 1] = order_key(x.y);
+        keys[i + 2] = order_key(x.z); keys[i + 3] = order_key(x.w);
+    }
+}
+
+__device__ __forceinline__ bool sample_row_few(const float* row, int V, double T, double p, NucleusCuts cuts, double u,
+                                               double* s_hist, double* s_tot, double* s_d, int* s_i, float* s_f,
+                                               float* row_max, int* out) {
     __shared__ int s_cnt[kCPT * kWaves];
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
     const __amdgpu_buffer_rsrc_t rs = buf_rsrc(row, (uint32_t)V * 4);   // reads past V are not made
@@ -753,50 +782,84 @@ __device__ __forceinline__ bool sample_row_few(const float* row, int V, double T
         const BufOffset o = nucleus_read(i, t);
         v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, o.voff, o.soff, 0));
     }
-    uint32_t kmax = 0;
+    float vmax = -INFINITY;
 #pragma unroll
     for (int i = 0; i < kCPT; ++i) {
         if (i * kNT + t >= V) v[i] = -INFINITY;
-        kmax = max(kmax, order_key(v[i]));
+        vmax = fmaxf(vmax, v[i]);
+        reinterpret_cast<float*>(s_hist)[row_slot(t) + i * kNT] = v[i];   // kNT is a multiple of 256: row_slot(t + i kNT)
     }
-    const float lmax = block_max_f(key_value(kmax), s_f);
+    const float lmax = block_max_f(vmax, s_f);
+    *row_max = lmax;
     const double r = 1.0 / T, zmax = (double)lmax / T;
-    const uint32_t kh = order_key(lmax), k9 = order_key((float)((double)lmax - 9.0 * T));
-    auto weight = [&](uint32_t key) { return exp_neg(div_by((double)key_value(key), T, r) - zmax); };
-    double tot[2] = {0.0, 0.0};   // of all ids; of those below k9
+    const float f1 = (float)((double)lmax - cuts.first * T), f2 = (float)((double)lmax - cuts.second * T);
+    // ids at or above f: their number, and in s_cnt the place in id order of each (tile, wave)'s first
+    auto places = [&](float f) {
 #pragma unroll
-    for (int i = 0; i < kCPT; ++i) {
-        const uint32_t key = order_key(v[i]);
-        const double e = i * kNT + t < V ? weight(key) : 0.0;
-        tot[0] += e;
-        tot[1] += key < k9 ? e : 0.0;
-        if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // 32 exponentials interleaved would spill
+        for (int i = 0; i < kCPT; ++i) {
+            const uint64_t b = __ballot(i * kNT + t < V && v[i] >= f);
+            if (lane == 0) s_cnt[i * kWaves + wave] = __popcll(b);
+        }
+        __syncthreads();
+        int n;
+        const int mine = t < kCPT * kWaves ? s_cnt[t] : 0;
+        const int base = block_exscan_total_i(mine, s_i, &n);
+        if (t < kCPT * kWaves) s_cnt[t] = base;
+        __syncthreads();
+        return n;
+    };
+    float fl = f1;
+    int total = places(f1);
+    bool few = total <= kNT * kFew;
+    if (few && total > kNT * kFew / 4) {   // will the first cut hold?  A float32 sum, which decides nothing but the route
+        const float c1 = (float)(r * 1.4426950408889634), c0 = (float)(zmax * 1.4426950408889634);
+        float f[2] = {0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < kCPT; ++i) {
+            const float e = __builtin_amdgcn_exp2f(fmaf(v[i], c1, -c0));
+            f[0] += e;
+            f[1] += v[i] < f1 ? e : 0.f;
+        }
+        double fs[2] = {f[0], f[1]};
+        block_sum_d<2>(fs, s_d);
+        if (fs[1] > (1.0 - p) * fs[0]) {
+            int n = 0;
+#pragma unroll
+            for (int i = 0; i < kCPT; ++i) n += v[i] >= f2;
+            few = block_sum_i(n, s_i) <= kNT * kFew;   // else the exact sums below decide
+        }
     }
-    block_sum_d<2>(tot, s_d);
-    // a NaN or infinite logit, a row of -inf, an infinite T: no threshold to find here (the division below serves T = inf)
-    if (!__builtin_isfinite(tot[0])) return false;
+    // what the passes above formed of the row is not kept for those below: it would spill
+#pragma unroll
+    for (int i = 0; i < kCPT; ++i) asm volatile("" : "+v"(v[i]));
+    auto weight = [&](float x) { return exp_neg(div_by((double)x, T, r) - zmax); };
+    double tot[2] = {0.0, 0.0};   // of all ids; of those below f1
+    if (few) {
+#pragma unroll
+        for (int i = 0; i < kCPT; ++i) {
+            const double e = i * kNT + t < V ? weight(v[i]) : 0.0;
+            tot[0] += e;
+            tot[1] += v[i] < f1 ? e : 0.0;
+            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // 32 exponentials interleaved would spill
+        }
+        block_sum_d<2>(tot, s_d);
+        // a NaN or infinite logit, a row of -inf, an infinite T: no threshold to find here (sample_row's division serves T = inf)
+        few = __builtin_isfinite(tot[0]);
+        if (few && !(tot[1] <= (1.0 - p) * tot[0] * (1.0 - 1e-9))) {
+            fl = f2;
+            total = places(f2);
+            few = total <= kNT * kFew;
+        }
+    }
     const double pE = p * tot[0];
-    const uint32_t kl = tot[1] <= (1.0 - p) * tot[0] * (1.0 - 1e-9)
-                            ? k9 : order_key((float)((double)lmax + T * (log((1.0 - p) / V) - 1.0)));
-    // candidates per (tile, wave), then each one's place in id order
-#pragma unroll
-    for (int i = 0; i < kCPT; ++i) {
-        const uint64_t b = __ballot(i * kNT + t < V && order_key(v[i]) >= kl);
-        if (lane == 0) s_cnt[i * kWaves + wave] = __popcll(b);
-    }
-    __syncthreads();
-    int total;
-    const int mine = t < kCPT * kWaves ? s_cnt[t] : 0;
-    const int base = block_exscan_total_i(mine, s_i, &total);
-    if (t < kCPT * kWaves) s_cnt[t] = base;
-    __syncthreads();
-    if (total > kNT * kFew) return false;
+    if (!few) return false;   // the row in s_hist is whole: the barriers of places
     uint32_t* s_k = reinterpret_cast<uint32_t*>(s_hist);   // [kNT * kFew] keys, ids
     int* s_id = reinterpret_cast<int*>(s_k + kNT * kFew);
-    static_assert(kNT * kFew * 8 <= kBins * kNT * 8, "the candidates fit the histogram's memory");
+    static_assert(kNT * kFew * 8 <= kBins * kNT * 8 && kNT * kCPT * 4 <= kBins * kNT * 8 && kNT % 256 == 0,
+                  "the candidates, and the row, fit the histogram's memory");
 #pragma unroll
     for (int i = 0; i < kCPT; ++i) {
-        const bool in = i * kNT + t < V && order_key(v[i]) >= kl;
+        const bool in = i * kNT + t < V && v[i] >= fl;
         const uint64_t b = __ballot(in);
         if (in) {
             const int slot = s_cnt[i * kWaves + wave] + __popcll(b & ((1ull << lane) - 1));
@@ -817,10 +880,11 @@ __device__ __forceinline__ bool sample_row_few(const float* row, int V, double T
         fk[i] = in ? s_k[c] : 0u;
         fid[i] = in ? s_id[c] : 0;
         fe[i] = 0.0;
-        if (i < per) fe[i] = in ? weight(fk[i]) : 0.0;   // per is the same in every thread
+        if (i < per) fe[i] = in ? weight(key_value(fk[i])) : 0.0;   // per is the same in every thread
         if (in) kept |= 1u << i;
     }
     __syncthreads();
+    const uint32_t kh = order_key(lmax), kl = order_key(fl);
     uint32_t prefix = 0;
     int shift = 28;
     while (shift > 0 && (kl >> shift) == (kh >> shift)) shift -= 4;
@@ -829,20 +893,24 @@ __device__ __forceinline__ bool sample_row_few(const float* row, int V, double T
     return true;
 }
 
-__device__ __forceinline__ int sample_row(const float* row, int V, double T, double p, int top_k, double u) {
-    __shared__ double s_hist[kBins * kNT];   // 128 KiB: per-thread digit columns
+__device__ __forceinline__ int sample_row(const float* row, int V, double T, double p, int top_k, NucleusCuts cuts, double u) {
+    __shared__ __align__(16) double s_hist[kBins * kNT];   // 128 KiB: per-thread digit columns
     __shared__ double s_tot[kBins];          // digit totals (read by every thread after the last pass)
     __shared__ double s_d[2 * kWaves];
     __shared__ int s_i[kWaves];
     __shared__ float s_f[kWaves];
-    if ((top_k <= 0 || top_k >= V) && p < 1.0) {
-        int tok;
-        if (sample_row_few(row, V, T, p, u, s_hist, s_tot, s_d, s_i, s_f, &tok)) return tok;
-    }
     const int id0 = threadIdx.x * kCPT;
     // ids id0 .. id0+31 as order-preserving keys (the float is recovered from the key where needed)
     uint32_t keys[kCPT];
-    load_keys(row, V, id0, keys);
+    const bool plain = (top_k <= 0 || top_k >= V) && p < 1.0;
+    float lmax;
+    if (plain) {
+        int tok;
+        if (sample_row_few(row, V, T, p, cuts, u, s_hist, s_tot, s_d, s_i, s_f, &lmax, &tok)) return tok;
+        row_keys(s_hist, id0, keys);   // read by every thread before block_sum_d's barriers, s_hist is written after them
+    } else {
+        load_keys(row, V, id0, keys);
+    }
     Bits kept = 0;   // bit i: id0+i is kept by top-k
 #pragma unroll
     for (int i = 0; i < kCPT; ++i) if (id0 + i < V) kept |= 1u << i;
@@ -875,10 +943,12 @@ __device__ __forceinline__ int sample_row(const float* row, int V, double T, dou
         kept = nk;
     }
 
-    uint32_t kmax = 0;
+    if (!plain) {
+        uint32_t kmax = 0;
 #pragma unroll
-    for (int i = 0; i < kCPT; ++i) if ((kept >> i) & 1u) kmax = max(kmax, keys[i]);
-    const float lmax = block_max_f(key_value(kmax), s_f);
+        for (int i = 0; i < kCPT; ++i) if ((kept >> i) & 1u) kmax = max(kmax, keys[i]);
+        lmax = block_max_f(key_value(kmax), s_f);
+    }
     const double zmax = (double)lmax / T;
     double e[kCPT];
     double tot[1] = {0.0};
@@ -1065,7 +1135,7 @@ __device__ __forceinline__ int sample_row_chunked(const float* row, int V, doubl
 template <bool CHUNKED>
 __global__ void __launch_bounds__(kNT) verify_nucleus_kernel(const float* logits, int q, int V, const int* drafts,
                                                              int drafts_ld, float temperature, float top_p,
-                                                             int top_k, uint64_t seed, const int* pos0,
+                                                             int top_k, NucleusCuts cuts, uint64_t seed, const int* pos0,
                                                              const int* row_depth, int* tokens_out, int* n_accept,
                                                              int* counter) {
     __shared__ float s_val[kWaves];
@@ -1078,7 +1148,7 @@ __global__ void __launch_bounds__(kNT) verify_nucleus_kernel(const float* logits
     if (sample) {
         const double u = keyed_uniform(seed, b, pos0[b] + (row_depth ? row_depth[row] : j));
         if constexpr (CHUNKED) t = sample_row_chunked(lg, V, (double)temperature, (double)top_p, top_k, u);
-        else t = sample_row(lg, V, (double)temperature, (double)top_p, top_k, u);
+        else t = sample_row(lg, V, (double)temperature, (double)top_p, top_k, cuts, u);
     } else {
         t = block_argmax<kNT>(lg, V, s_val, s_idx);
     }
@@ -1092,7 +1162,7 @@ hipError_t launch_verify_nucleus(const float* logits, int B, int q, int V, const
     if (V > kChunk * kMaxChunks || (row_depth && drafts)) return hipErrorInvalidValue;
     auto kern = V > kChunk ? verify_nucleus_kernel<true> : verify_nucleus_kernel<false>;
     hipLaunchKernelGGL(kern, dim3(B * q), dim3(kNT), 0, s, logits, q, V, drafts, drafts_ld, temperature, top_p, top_k,
-                       seed, pos0, row_depth, tokens_out, n_accept, counter);
+                       nucleus_cuts(top_p, V), seed, pos0, row_depth, tokens_out, n_accept, counter);
     return hipGetLastError();
 }
 

@@ -41,6 +41,37 @@ def test_few(vocab, temp, p):
     ctx.close()
 
 
+# p; ids at each logit (the rest at -20) at T = 1, V = 32016.  First cut -9.0 (p 0.95) or -10.6 (p 0.99), second
+# -14.4 or -16.0; 8192 ids fit.
+ROUTES = {
+    "fits exactly": (0.95, {0.0: 1, -5.0: 8191, -9.2: 20000}),
+    "one too many": (0.95, {0.0: 1, -5.0: 8192, -9.2: 20000}),
+    "tail too heavy, second cut too many": (0.95, {0.0: 1, -5.0: 3000, -9.2: 29015}),
+    "tail too heavy, seen after the sums": (0.95, {0.0: 1, -5.0: 1000, -9.2: 31015}),
+    "second cut, few above the first": (0.99, {0.0: 1, -5.0: 100, -10.7: 5000}),
+    "second cut, many above the first": (0.99, {0.0: 1, -9.0: 2500, -10.7: 5000}),
+    "second cut fits exactly": (0.99, {0.0: 1, -5.0: 100, -10.7: 8091}),
+}
+
+
+@pytest.mark.parametrize("name", list(ROUTES))
+def test_routes(name):
+    """Rows on either side of each decision of the gathered sampler (levels spread a little, so that few ids tie)."""
+    p, levels = ROUTES[name]
+    vocab, rng = 32016, np.random.default_rng(7)
+    lg = np.full((4, vocab), -20.0, np.float32)
+    for row in lg:
+        ids, at = rng.permutation(vocab), 0
+        for level, n in levels.items():
+            row[ids[at:at + n]] = level + (0.05 * rng.random(n) if n > 1 else 0)
+            at += n
+    for seed in range(4):
+        got = _verify(lg, 1.0, p, seed)
+        for j in range(4):
+            want, margin = S.sample(lg[j], 1.0, float(np.float32(p)), 0, S.uniform(seed, 0, 17 + j))
+            assert got[j] == int(want) or margin < 1e-9, (name, seed, j)
+
+
 def _verify(lg, temp, p, seed):
     q, vocab = lg.shape
     sh = synth.small_shape(n_layers=1, vocab=vocab)
