@@ -77,9 +77,10 @@ AttnPlan plan_attention(int B, int H, int q, int head_dim, int max_len, int S_ma
     // takes one split: the key partition only has to be the same for every decode block size.
     p.row_tiles = (q + 15) / 16;
     int target = std::max(1, std::min(kMaxSplits, kAttnWorkgroups / pairs));
-    // A cache of at most 8 blocks gives each wave of one workgroup one block: splits would add their
-    // merge across workgroups and save nothing (tiny decoder, 128 slots: 9.4 -> 7.6 us per layer).
-    if (target <= 2 || q > kAttnSplitRows || cap <= kMaxWaves) target = 1;
+    // Where every split would hold one block, and a workgroup has a wave for each (at most 8), one split
+    // does: the same blocks are merged in the same order, in LDS instead of across workgroups (tiny
+    // decoder, 128 slots: 9.4 -> 7.6 us per layer).  Fewer splits than blocks merge in groups, another order.
+    if (target <= 2 || q > kAttnSplitRows || (cap <= kMaxWaves && cap <= target)) target = 1;
     p.per_split = (cap + target - 1) / target;
     p.splits = (nblk + p.per_split - 1) / p.per_split;
     p.waves = std::max(1, std::min(p.per_split, kMaxWaves));

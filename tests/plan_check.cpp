@@ -8,6 +8,7 @@
 //  2. Attention: the key partition (32-key blocks per split) and the waves per workgroup depend on
 //     the batch and the capacity only, never on the block rows or the cache length, for blocks of
 //     one 16-row tile (the decode blocks whose rows must match single-token steps bit for bit).
+//     Where one split takes the place of several, each of those held one block.
 //  3. Residual GEMMs: the partial-tile buffer (gemm_resid_part_bytes) holds every split plan of
 //     up to 64 rows.
 //  4. Skinny GEMMs: the contraction slices (waves x workgroups per tile) do not depend on the rows
@@ -48,6 +49,7 @@ int main() {
         {8, 32, 128, 11, 16427},   // micro-benchmark: 16384 keys, q 6 and 11
         {1, 2, 128, 64, 370}, {1, 2, 128, 16, 100}, {3, 2, 128, 6, 86}, {2, 4, 64, 17, 2000},
         {1, 4, 64, 64, 1200}, {2, 4, 128, 16, 1800}, {8, 2, 128, 70, 200},
+        {2, 32, 128, 64, 240}, {3, 20, 64, 64, 256},   // short caches: 7 and 8 blocks, 4 to 12 splits
     };
     for (const Cfg& c : cfgs) {
         const int S = (c.max_ctx + 31) / 32 * 32;
@@ -64,6 +66,14 @@ int main() {
                               p.per_split >= 1 && (long)p.splits * p.per_split * 32 >= std::min(S, len + q),
                           "attention plan shape: B %d q %d len %d", B, q, len);
                     if (q <= kAttnSplitRows) {
+                        // blocks per split at full capacity: as many splits as make one round of 256 workgroups, 16 at
+                        // most, one where that is two.  One split may stand for splits of a block each: a wave each,
+                        // merged in the same order
+                        const int cap = std::max(1, S / 32), most = std::max(1, std::min(16, 256 / (B * c.H)));
+                        const int per = (cap + (most <= 2 ? 1 : most) - 1) / (most <= 2 ? 1 : most);
+                        CHECK(p.per_split == per || (per == 1 && p.per_split == cap && p.splits == 1 && p.waves == cap),
+                              "order of the key blocks: B %d H %d q %d S %d: %d per split, %d waves (%d)", B, c.H, q, S,
+                              p.per_split, p.waves, per);
                         CHECK(p.per_split == ref.per_split && p.waves == ref.waves,
                               "key partition varies with the block: B %d q %d len %d (%d/%d waves %d/%d)", B, q, len,
                               p.per_split, ref.per_split, p.waves, ref.waves);
