@@ -209,23 +209,21 @@ __device__ __forceinline__ Frag<T> a_frag(const XT& x, float inv) {
 }
 
 // One batch of U contraction steps: the weight fragments of the NTW tiles
-// (streamed, non-temporal) and the X fragments of every row tile.  TAIL
-// batches may run past the wave's slice: those steps reload the last step
-// with X zeroed.  Loads of the steady-state loop are unconditional so that
-// the compiler's wait counts stay exact and two batches really are in flight.
-template <typename T, typename XT, int MT, int NTW, int U, bool TAIL>
+// (streamed, non-temporal) and the X fragments of every row tile.  Steps past
+// the wave's slice reload the last step with X zeroed.
+template <typename T, typename XT, int MT, int NTW, int U>
 __device__ __forceinline__ void load_batch(Frag<T> (&w)[U][NTW], XT (&x)[U][MT], const T* const (&wp)[NTW],
                                            __amdgpu_buffer_rsrc_t xrs, const uint32_t (&xo)[MT],
                                            const uint32_t (&xst)[MT], int s, int nks) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int st = TAIL ? min(s + u, nks - 1) : s + u;
+        const int st = min(s + u, nks - 1);
 #pragma unroll
         for (int j = 0; j < NTW; ++j) w[u][j] = Frag<T>::load_nt(wp[j] + (size_t)st * 512);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             x[u][mt] = buf_frag<typename XT::elem>(xrs, xo[mt], (uint32_t)st * xst[mt]);
-            if (TAIL && s + u >= nks) x[u][mt] = XT::zero();
+            if (s + u >= nks) x[u][mt] = XT::zero();
         }
     }
 }
@@ -241,6 +239,35 @@ __device__ __forceinline__ void mma_batch(f32x4_t (&acc)[NTW][MT], const Frag<T>
 #pragma unroll
             for (int j = 0; j < NTW; ++j) mma(acc[j][mt], xa, w[u][j]);
         }
+}
+
+// The steady state: a batch's products, each step's fragments reloaded with the
+// step two batches ahead (s + u, inside the slice) as soon as they are used.
+// The loads are unconditional so that the compiler's wait counts stay exact, and
+// each step is kept together: with the row step a run-time value the scheduler
+// puts a whole batch's loads behind its products, X before W, and the stream
+// stalls (7B, 4 layers, 1 / 2 / 6 rows: 409.4 / 416.7 / 430 us, so 398.7 / 412 /
+// 426; with the row step a constant, in an instance for one row: 400 / 415.6 / 429).
+template <typename T, bool XF, typename XT, int MT, int NTW, int U>
+__device__ __forceinline__ void step_batch(f32x4_t (&acc)[NTW][MT], Frag<T> (&w)[U][NTW], XT (&x)[U][MT],
+                                           const float (&inv)[MT], const T* const (&wp)[NTW],
+                                           __amdgpu_buffer_rsrc_t xrs, const uint32_t (&xo)[MT],
+                                           const uint32_t (&xst)[MT], int s) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const Frag<T> xa = a_frag<T, XF>(x[u][mt], inv[mt]);
+#pragma unroll
+            for (int j = 0; j < NTW; ++j) mma(acc[j][mt], xa, w[u][j]);
+        }
+#pragma unroll
+        for (int j = 0; j < NTW; ++j) w[u][j] = Frag<T>::load_nt(wp[j] + (size_t)(s + u) * 512);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            x[u][mt] = buf_frag<typename XT::elem>(xrs, xo[mt], (uint32_t)(s + u) * xst[mt]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 // Fused epilogue of one reduced 16 x 16 tile (column tile `tile`, row tile mt), run by one wave.
@@ -432,8 +459,8 @@ __global__ void __launch_bounds__(NTW > 1 ? 256 : 512) gemm_kernel(GemmArgs a) {
         xr[mt] = c < rows ? ((uint32_t)(16 * mt) * a.ldx + ((ks0 * 4 + g) * rows + c) * 8) * xes : x_bytes;
     }
     if (nks > 0) {
-        load_batch<T, XT, MT, NTW, U, true>(w0, x0, wp, xrs, xr, xst, 0, nks);
-        load_batch<T, XT, MT, NTW, U, true>(w1, x1, wp, xrs, xr, xst, U, nks);
+        load_batch<T, XT, MT, NTW, U>(w0, x0, wp, xrs, xr, xst, 0, nks);
+        load_batch<T, XT, MT, NTW, U>(w1, x1, wp, xrs, xr, xst, U, nks);
     }
 
     // row scales 1/rms, needed before the first matrix-core step (rows past
@@ -467,18 +494,16 @@ __global__ void __launch_bounds__(NTW > 1 ? 256 : 512) gemm_kernel(GemmArgs a) {
         // flight; each is refilled with the batch two ahead once consumed
         int s = 0;
         for (; s + 4 * U <= nks; s += 2 * U) {
-            mma_batch<T, XF, XT, MT, NTW, U>(acc, w0, x0, inv);
-            load_batch<T, XT, MT, NTW, U, false>(w0, x0, wp, xrs, xr, xst, s + 2 * U, nks);
-            mma_batch<T, XF, XT, MT, NTW, U>(acc, w1, x1, inv);
-            load_batch<T, XT, MT, NTW, U, false>(w1, x1, wp, xrs, xr, xst, s + 3 * U, nks);
+            step_batch<T, XF, XT, MT, NTW, U>(acc, w0, x0, inv, wp, xrs, xr, xst, s + 2 * U);
+            step_batch<T, XF, XT, MT, NTW, U>(acc, w1, x1, inv, wp, xrs, xr, xst, s + 3 * U);
         }
         // tail: steps s .. nks-1 (fewer than 4U), the first two batches loaded
         // (unconditional refills here, or one straight-line path per remaining
         // count, measured slower on MI355X)
         mma_batch<T, XF, XT, MT, NTW, U>(acc, w0, x0, inv);
-        if (s + 2 * U < nks) load_batch<T, XT, MT, NTW, U, true>(w0, x0, wp, xrs, xr, xst, s + 2 * U, nks);
+        if (s + 2 * U < nks) load_batch<T, XT, MT, NTW, U>(w0, x0, wp, xrs, xr, xst, s + 2 * U, nks);
         if (s + U < nks) mma_batch<T, XF, XT, MT, NTW, U>(acc, w1, x1, inv);
-        if (s + 3 * U < nks) load_batch<T, XT, MT, NTW, U, true>(w1, x1, wp, xrs, xr, xst, s + 3 * U, nks);
+        if (s + 3 * U < nks) load_batch<T, XT, MT, NTW, U>(w1, x1, wp, xrs, xr, xst, s + 3 * U, nks);
         if (s + 2 * U < nks) mma_batch<T, XF, XT, MT, NTW, U>(acc, w0, x0, inv);
         if (s + 3 * U < nks) mma_batch<T, XF, XT, MT, NTW, U>(acc, w1, x1, inv);
     }
