@@ -734,25 +734,28 @@ __device__ __forceinline__ int finish_row(const uint32_t (&keys)[N], const doubl
 
 // Top-p without top-k, the usual case: only the ids that can be in the nucleus are kept.  Consecutive threads
 // hold consecutive ids (32 tiles of 1024); the total mass takes every id, and
-//  * the ids below lmax - T (6 - ln(1 - p)) (9 T at p 0.95), where they hold at most (1 - p) of the mass, or
+//  * the ids below a first cut, 9 T under lmax at p 0.95, where they hold at most (1 - p) of the mass, or
 //  * those below lmax - T (1 - ln((1 - p) / V)) otherwise (the ids at or below the threshold hold at least
 //    (1 - p) E >= 1 - p, none more than the threshold's own weight, so that weight is at least (1 - p) / V;
 //    the 1 is for rounding)
 // neither move the threshold nor are in the nucleus (std-4 logits, T 0.8, p 0.95: 1000 of 32016 are left).
 // The others are gathered in id order, kFew to a thread, and digits in which the range's ends agree need no
 // pass.  sample_row below keeps 32 ids per thread through every step; its code, unrolled for that, is
-// fetched once per launch and took most of its 66 us.  4 x 6 rows of 32016 ids: 66.5 -> 43.8 us.
+// fetched once per launch and took most of its 66 us.  4 x 6 rows of 32016 ids: 66.5 -> 42.9 us.
 // Flat rows leave more than kNT kFew ids (std 1.3, T 0.8, p 0.95: 29000 of 32016; their nucleus alone is 16000)
 // and go to sample_row.  That is seen before the float64 exponentials are paid for: the ids above the first cut
-// are counted and placed first, and where they are many a float32 sum says whether that cut will hold.  The row
-// waits in s_hist for sample_row, whose own load, 128 bytes apart per lane, costs more than this one.  4 x 6
-// rows of std 1.3 / 2 / 3 / 4: 71.0 / 71.3 / 49.2 / 43.8 us (with the exponentials before the count 89.1 / 88.5 /
-// 45.9 / 42.8, by sample_row alone 68.9 / 68.1 / 68.2 / 66.5).
+// are counted and placed first, and where that is more than one per thread a float32 sum says whether the cut
+// will hold.  The row waits in s_hist for sample_row, whose own load, 128 bytes apart per lane, costs more than
+// this one.  4 x 6 rows of std 1.3 / 2 / 3 / 4: 67.2 / 70.5 / 48.6 / 42.9 us (with the exponentials before the
+// count 89.1 / 88.5 / 45.9 / 42.8, by sample_row alone 68.7 / 68.3 / 68.2 / 66.5).
+// First cut: near the highest that holds for normal logits of a standard deviation of 2 to 5 T.  Beyond p 0.95 the
+// mass left out has to shrink faster than the second cut falls (p 0.99, std 4, T 0.8: 67.1 us where it is 10.6 T,
+// 49.9 at 13 T); lower everywhere, it leaves more ids (10.5 T at p 0.95: 45.5 us for the 43.8).
 // Returns false (nothing decided) when too many ids are left or the total mass is not finite.
 struct NucleusCuts { double first, second; };   // in units of T below the largest logit
 static NucleusCuts nucleus_cuts(float top_p, int V) {
-    const double rest = 1.0 - std::min((double)top_p, 1.0);
-    return {6.0 - std::log(rest), 1.0 - std::log(rest / V)};
+    const double rest = 1.0 - std::min((double)top_p, 1.0), l = -std::log(rest);
+    return {6.0 + l + 1.5 * std::max(0.0, l - 3.0), 1.0 - std::log(rest / V)};
 }
 
 __device__ __forceinline__ int row_slot(int id) {   // runs of 32 ids, a thread's of sample_row; quads permuted by run against bank conflicts
@@ -811,7 +814,7 @@ __device__ __forceinline__ bool sample_row_few(const float* row, int V, double T
     float fl = f1;
     int total = places(f1);
     bool few = total <= kNT * kFew;
-    if (few && total > kNT * kFew / 4) {   // will the first cut hold?  A float32 sum, which decides nothing but the route
+    if (few && total > kNT) {   // will the first cut hold?  A float32 sum, which decides nothing but the route
         const float c1 = (float)(r * 1.4426950408889634), c0 = (float)(zmax * 1.4426950408889634);
         float f[2] = {0.f, 0.f};
 #pragma unroll
@@ -893,6 +896,9 @@ __device__ __forceinline__ bool sample_row_few(const float* row, int V, double T
     return true;
 }
 
+// PLAIN: top-p below 1 without top-k.  An instance of its own, as each of the two paths costs the other registers
+// (top-k 10, 6 rows: 22.7 us with both in one kernel, 21.6 apart; top-k 50: 84.2, 82.0).
+template <bool PLAIN>
 __device__ __forceinline__ int sample_row(const float* row, int V, double T, double p, int top_k, NucleusCuts cuts, double u) {
     __shared__ __align__(16) double s_hist[kBins * kNT];   // 128 KiB: per-thread digit columns
     __shared__ double s_tot[kBins];          // digit totals (read by every thread after the last pass)
@@ -902,9 +908,8 @@ __device__ __forceinline__ int sample_row(const float* row, int V, double T, dou
     const int id0 = threadIdx.x * kCPT;
     // ids id0 .. id0+31 as order-preserving keys (the float is recovered from the key where needed)
     uint32_t keys[kCPT];
-    const bool plain = (top_k <= 0 || top_k >= V) && p < 1.0;
     float lmax;
-    if (plain) {
+    if constexpr (PLAIN) {
         int tok;
         if (sample_row_few(row, V, T, p, cuts, u, s_hist, s_tot, s_d, s_i, s_f, &lmax, &tok)) return tok;
         row_keys(s_hist, id0, keys);   // read by every thread before block_sum_d's barriers, s_hist is written after them
@@ -915,35 +920,34 @@ __device__ __forceinline__ int sample_row(const float* row, int V, double T, dou
 #pragma unroll
     for (int i = 0; i < kCPT; ++i) if (id0 + i < V) kept |= 1u << i;
 
-    // k up to 3/4 of the list: the candidates (about k) rarely overflow it
-    if (top_k > 0 && top_k <= kSmallK * 3 / 4 && top_k < V) {
-        int tok;
-        if (sample_small_topk(keys, kept, id0, T, p, top_k, u, s_i, &tok)) return tok;
-    }
-    if (top_k > 0 && top_k < V) {
-        // largest key Kk with count(key >= Kk) >= top_k (counts are exact in double)
-        double cnt;
-        const uint32_t Kk = radix_threshold(keys, kept, [&](int) { return 1.0; }, (double)top_k, s_hist, s_tot, &cnt);
-        int gt = 0, eq = 0;
-#pragma unroll
-        for (int i = 0; i < kCPT; ++i) {
-            if (!((kept >> i) & 1u)) continue;
-            gt += keys[i] > Kk;
-            eq += keys[i] == Kk;
+    if constexpr (!PLAIN) {
+        // k up to 3/4 of the list: the candidates (about k) rarely overflow it
+        if (top_k > 0 && top_k <= kSmallK * 3 / 4 && top_k < V) {
+            int tok;
+            if (sample_small_topk(keys, kept, id0, T, p, top_k, u, s_i, &tok)) return tok;
         }
-        const int need = top_k - block_sum_i(gt, s_i);
-        int rank = block_exscan_i(eq, s_i);
-        Bits nk = 0;
+        if (top_k > 0 && top_k < V) {
+            // largest key Kk with count(key >= Kk) >= top_k (counts are exact in double)
+            double cnt;
+            const uint32_t Kk = radix_threshold(keys, kept, [&](int) { return 1.0; }, (double)top_k, s_hist, s_tot, &cnt);
+            int gt = 0, eq = 0;
 #pragma unroll
-        for (int i = 0; i < kCPT; ++i) {
-            if (!((kept >> i) & 1u)) continue;
-            if (keys[i] > Kk) nk |= 1u << i;
-            else if (keys[i] == Kk) { if (rank < need) nk |= 1u << i; ++rank; }
+            for (int i = 0; i < kCPT; ++i) {
+                if (!((kept >> i) & 1u)) continue;
+                gt += keys[i] > Kk;
+                eq += keys[i] == Kk;
+            }
+            const int need = top_k - block_sum_i(gt, s_i);
+            int rank = block_exscan_i(eq, s_i);
+            Bits nk = 0;
+#pragma unroll
+            for (int i = 0; i < kCPT; ++i) {
+                if (!((kept >> i) & 1u)) continue;
+                if (keys[i] > Kk) nk |= 1u << i;
+                else if (keys[i] == Kk) { if (rank < need) nk |= 1u << i; ++rank; }
+            }
+            kept = nk;
         }
-        kept = nk;
-    }
-
-    if (!plain) {
         uint32_t kmax = 0;
 #pragma unroll
         for (int i = 0; i < kCPT; ++i) if ((kept >> i) & 1u) kmax = max(kmax, keys[i]);
@@ -961,8 +965,11 @@ __device__ __forceinline__ int sample_row(const float* row, int V, double T, dou
     const double pE = (p < 1.0 ? p : 1.0) * tot[0];
 
     // top-p threshold key and the mass of the nucleus
-    double mass;
-    const uint32_t Kstar = radix_threshold(keys, kept, [&](int i) { return e[i]; }, pE, s_hist, s_tot, &mass);
+    double mass = pE;
+    uint32_t Kstar = 0;   // PLAIN without a finite mass: every id, and then the last (radix_threshold finds the same)
+    auto w_of = [&](int i) { return e[i]; };
+    if constexpr (!PLAIN) Kstar = radix_threshold(keys, kept, w_of, pE, s_hist, s_tot, &mass);
+    else if (__builtin_isfinite(pE)) Kstar = radix_refine<kCPT>(keys, kept, w_of, pE, 0u, 28, s_hist, s_tot, s_i, &mass);
 
     // inverse CDF over the nucleus in ascending id order
     double loc = 0.0;
@@ -1132,7 +1139,8 @@ __device__ __forceinline__ int sample_row_chunked(const float* row, int V, doubl
     return block_max_i(last, s_i);
 }
 
-template <bool CHUNKED>
+enum NucleusMode { NUCLEUS_PLAIN, NUCLEUS_GENERAL, NUCLEUS_CHUNKED };
+template <NucleusMode MODE>
 __global__ void __launch_bounds__(kNT) verify_nucleus_kernel(const float* logits, int q, int V, const int* drafts,
                                                              int drafts_ld, float temperature, float top_p,
                                                              int top_k, NucleusCuts cuts, uint64_t seed, const int* pos0,
@@ -1147,8 +1155,8 @@ __global__ void __launch_bounds__(kNT) verify_nucleus_kernel(const float* logits
     int t;
     if (sample) {
         const double u = keyed_uniform(seed, b, pos0[b] + (row_depth ? row_depth[row] : j));
-        if constexpr (CHUNKED) t = sample_row_chunked(lg, V, (double)temperature, (double)top_p, top_k, u);
-        else t = sample_row(lg, V, (double)temperature, (double)top_p, top_k, cuts, u);
+        if constexpr (MODE == NUCLEUS_CHUNKED) t = sample_row_chunked(lg, V, (double)temperature, (double)top_p, top_k, u);
+        else t = sample_row<MODE == NUCLEUS_PLAIN>(lg, V, (double)temperature, (double)top_p, top_k, cuts, u);
     } else {
         t = block_argmax<kNT>(lg, V, s_val, s_idx);
     }
@@ -1160,7 +1168,9 @@ hipError_t launch_verify_nucleus(const float* logits, int B, int q, int V, const
                                  float temperature, float top_p, int top_k, uint64_t seed, const int* pos0,
                                  int* tokens_out, int* n_accept, int* counter, hipStream_t s, const int* row_depth) {
     if (V > kChunk * kMaxChunks || (row_depth && drafts)) return hipErrorInvalidValue;
-    auto kern = V > kChunk ? verify_nucleus_kernel<true> : verify_nucleus_kernel<false>;
+    const bool plain = (top_k <= 0 || top_k >= V) && top_p < 1.f;
+    auto kern = V > kChunk ? verify_nucleus_kernel<NUCLEUS_CHUNKED>
+                : plain    ? verify_nucleus_kernel<NUCLEUS_PLAIN> : verify_nucleus_kernel<NUCLEUS_GENERAL>;
     hipLaunchKernelGGL(kern, dim3(B * q), dim3(kNT), 0, s, logits, q, V, drafts, drafts_ld, temperature, top_p, top_k,
                        nucleus_cuts(top_p, V), seed, pos0, row_depth, tokens_out, n_accept, counter);
     return hipGetLastError();
