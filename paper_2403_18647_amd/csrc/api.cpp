@@ -204,7 +204,7 @@ void carve(sdsat_ctx* c, Carver& cv) {
     c->cache_len = (int*)cv.take((size_t)D.maxB * 4);
     c->err_flag = (int*)cv.take(4);
     c->verify_cnt = (int*)cv.take((size_t)D.maxB * 4);
-    c->verify_best = (unsigned long long*)cv.take((size_t)D.maxM * 8);
+    c->verify_best = (unsigned long long*)cv.take((size_t)D.maxM * 8);   // right behind verify_cnt: cleared with it
     c->produced = (int*)cv.take((size_t)D.maxB * 4);
     c->loop_rec = (int*)cv.take((size_t)kRecLoops * D.maxB * kLoopRecCols * 4);
     const size_t bq = (size_t)D.maxB * D.maxQ;
@@ -642,8 +642,8 @@ int sdsat_init(const sdsat_config* cfg, const void* const* weights, int32_t n_we
         (void)launch_fill_i32((int*)c->obuf, m16 * D.d_pad * D.esz / 4, 0, c->stream);
         (void)launch_fill_i32((int*)c->ubuf, m16 * D.F_pad * D.esz / 4, 0, c->stream);
         (void)launch_fill_i32((int*)c->hbuf, m16 * D.d_pad * D.esz / 4, 0, c->stream);
-        (void)launch_fill_i32(c->verify_cnt, D.maxB, 0, c->stream);
-        (void)launch_fill_i32((int*)c->verify_best, (size_t)D.maxM * 2, 0, c->stream);
+        // verify_cnt and verify_best: neighbours in the workspace, one launch
+        (void)launch_fill_i32(c->verify_cnt, (size_t)((int*)(c->verify_best + D.maxM) - c->verify_cnt), 0, c->stream);
         (void)launch_fill_i32(c->attn_ctr, attention_counter_ints(D.maxB, D.H, D.maxQ), 0, c->stream);
         (void)launch_fill_i32(c->cache_len, D.maxB, 0, c->stream);
         (void)launch_fill_i32(c->err_flag, 1, 0, c->stream);
