@@ -214,22 +214,29 @@ __device__ __forceinline__ void attend_block(const Frag<T> (&kf)[2][NDS], const 
     }
 }
 
-// Columns d .. d + 3 of head h (d a multiple of 4) of block row m: float rows,
-// or the O GEMM's input in fragment order (the four stay in one chunk).
-template <typename T, int DH>
-__device__ __forceinline__ void store_out(const AttnArgs& a, int b, int h, int m, int d, f32x4_t v) {
+// Where columns d .. d + 3 of head h (d a multiple of 4) of block row m go: float
+// rows, or the O GEMM's input in fragment order (the four stay in one chunk).
+// The row is opaque, so that the offset is formed where this stands and not ahead
+// of the block loop: held through it, it takes attn_kernel<bf16, 128, 1> past its
+// 256 registers, and every launch then pays for scratch (1024 wide, 8 heads, one
+// row, 300 keys: 11.0 -> 10.5 us).
+template <int DH>
+__device__ __forceinline__ size_t out_off(const AttnArgs& a, int b, int h, int m, int d) {
     int row = b * a.q + m;
     const int col = h * DH + d;
+    asm volatile("" : "+v"(row));
+    return a.out_f32 ? (size_t)row * a.ldo + col : frag_off(row, col, a.ldo, a.out_rows);
+}
+
+template <typename T>
+__device__ __forceinline__ void store_out(const AttnArgs& a, size_t off, f32x4_t v) {
     if (a.out_f32) {
-        float* po = reinterpret_cast<float*>(a.out) + (size_t)row * a.ldo + col;   // the caller's: float-aligned
+        float* po = reinterpret_cast<float*>(a.out) + off;   // the caller's: float-aligned
 #pragma unroll
         for (int r = 0; r < 4; ++r) po[r] = v[r];
         return;
     }
-    // The offset is formed here, not ahead of the block loop: held through it, it takes attn_kernel<bf16, 128, 1> past
-    // its 256 registers, and every launch then pays for scratch (1024 wide, 8 heads, one row, 300 keys: 11.0 -> 10.5 us)
-    asm volatile("" : "+v"(row));
-    T* po = reinterpret_cast<T*>(a.out) + frag_off(row, col, a.ldo, a.out_rows);
+    T* po = reinterpret_cast<T*>(a.out) + off;
     if constexpr (sizeof(T) == 2)
         *reinterpret_cast<uint2*>(po) = uint2{f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3])};
     else
@@ -250,6 +257,7 @@ __device__ __forceinline__ void combine_tile(const AttnArgs& a, int bh, int rt, 
     for (int e = threadIdx.x; e < 16 * D4; e += blockDim.x) {
         const int m = 16 * rt + e / D4, d = 4 * (e % D4);
         if (m >= a.q) continue;
+        const size_t off = out_off<DH>(a, b, h, m, d);   // beside the loads
         const float* base = a.part + ((size_t)bh * a.splits * rows + m) * (DH + 4);
         float mx[kMaxSplits], sm[kMaxSplits];
         f32x4_t ov[kMaxSplits];
@@ -278,7 +286,7 @@ __device__ __forceinline__ void combine_tile(const AttnArgs& a, int bh, int rt, 
             }
         }
         const float inv = 1.0f / den;
-        store_out<T, DH>(a, b, h, m, d, acc * inv);
+        store_out<T>(a, off, acc * inv);
     }
 }
 
@@ -466,7 +474,7 @@ __global__ void __launch_bounds__(512) attn_kernel(AttnArgs a) {
                 continue;
             }
             const float inv = 1.0f / den;
-            store_out<T, DH>(a, b, h, m, d, acc * inv);
+            store_out<T>(a, out_off<DH>(a, b, h, m, d), acc * inv);
         }
     }
     if (a.splits > 1) {
@@ -631,7 +639,7 @@ __global__ void __launch_bounds__(64 * kRowWaves) attn_rows_kernel(AttnArgs a) {
     const float inv = 1.0f / (a0 * rsum + a1 * s1);
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
-        store_out<T, DH>(a, b, h, m, 16 * dt + 4 * g, (o[dt] * a0 + m_o[dt * 64 + lane] * a1) * inv);
+        store_out<T>(a, out_off<DH>(a, b, h, m, 16 * dt + 4 * g), (o[dt] * a0 + m_o[dt * 64 + lane] * a1) * inv);
 }
 
 // The same for bf16: one workgroup of 4 / RT pairs of waves per (sequence, head,
@@ -876,7 +884,7 @@ __global__ void __launch_bounds__(512 / RT, 2) attn_tiles_kernel(AttnArgs a) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[r] = fmaf(ov[r], w[k], acc[r]);
             }
-            store_out<T, DH>(a, b, h, m, 16 * dt + 4 * g, acc * inv);
+            store_out<T>(a, out_off<DH>(a, b, h, m, 16 * dt + 4 * g), acc * inv);
         }
     }
 }
