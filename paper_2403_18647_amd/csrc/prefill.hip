@@ -1,16 +1,15 @@
-// Row-wise kernels around the matrix-core GEMMs of large blocks (prompt prefill).
+// Row-wise kernels: the residual stream and the RMSNorm around the GEMMs.
 //
-// A block of more than 64 rows is weight-reuse bound rather than weight-stream
-// bound, so its linear layers run as tiled matrix-core GEMMs (prefill_gemm.hip:
-// bf16 or float inputs, float accumulation and output) on the caller's
-// row-major weights.  RoPE with the Q / K / V writes and SwiGLU run in the
-// epilogues of those GEMMs; the RMSNorm and the residual stream run here.
-// Both round exactly where the decode kernels round (the values a bf16 model
+// Decode blocks (at most 64 rows) use rms_rows, and norm_rows behind a split
+// residual GEMM.  A block of more rows (prompt prefill) is weight-reuse bound
+// rather than weight-stream bound, so its linear layers run as tiled matrix-core
+// GEMMs (prefill_gemm.hip: bf16 on the packed weights, float on the caller's
+// row-major ones, float accumulation and output).  RoPE with the Q / K / V
+// writes and SwiGLU run in the epilogues of those GEMMs, everything else of it
+// in norm_rows.  All round exactly where the decode kernels round (the values a bf16 model
 // stores): the RMSNorm output bf16(x o g / rms), K and V, the SwiGLU product;
 // Q and the residual stream stay float.  Rotary cos / sin come from the same
 // table as the decode path.
-#include <algorithm>
-
 #include <hip/hip_ext.h>
 
 #include "device.h"
@@ -19,55 +18,27 @@
 namespace sdsat {
 
 // h[m][k] = elem(xg[m][k] / rms_m), rms_m = sqrt(sum_t ssq[m][t] / K + eps),
-// xg and h in fragment order: a thread takes one 8-element chunk of a row, so
-// reads and writes are both contiguous.  A workgroup covers 512 chunks of one
-// 16-row tile; its values are requested first, then the waves sum the tile's
-// rows' partials in the order the decode GEMM does (lane-strided, then a wave
-// butterfly).  Latency-bound: 8 waves reduce at most two rows each (with 4 waves
-// of four rows the 7B 4-layer block of 6 rows took 420 us, now 415, the 13B
-// 3-layer block of 11 rows 504, now 499).
-static constexpr int kRmsThreads = 512;
+// xg and h in fragment order.  One wave per row and 64 of its 8-element chunks,
+// which sums the row's partials for itself, in the order the decode GEMM does
+// (lane-strided, then a wave butterfly).  Latency-bound: no barrier, and one
+// round trip for the values and the first partials.  With 8 waves per 512 chunks
+// of a 16-row tile (contiguous stores, but two rows' sums per wave and a barrier)
+// blocks of 9 rows took, us, 256 wide, 2 heads, 4 layers: 156, now 151; 1024 wide:
+// 188, now 182; the 7B 4-layer block of 6 rows 411.4, now 410.9; the 13B 3-layer
+// block of 11 rows 498.2, now 497.4.
 template <typename T>
-__global__ void __launch_bounds__(kRmsThreads) rms_rows_kernel(const float* xg, int ld, const float* ssq, int n_ssq, int K,
-                                                       float eps, int M, T* h) {
-    __shared__ float s_inv[16];
-    const int tile = blockIdx.y, rows = min(16, M - 16 * tile);
-    constexpr int NW = kRmsThreads / 64, RW = 16 / NW;   // waves, rows per wave
-    const int e = blockIdx.x * kRmsThreads + threadIdx.x;   // (chunk, row of the tile)
-    const bool mine = e < rows * (K / 8);
-    const size_t off = (size_t)tile * 16 * ld + (size_t)e * 8;
-    Frag<float> v = Frag<float>::zero();
-    if (mine) v = Frag<float>::load(xg + off);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    float sq[RW][4], sum[RW];   // this wave's rows: wave, wave + NW, ..
-#pragma unroll
-    for (int j = 0; j < RW; ++j) {
-        // the first 256 partials of every row are requested together (indices clamped into the array)
-        const float* sr = ssq + (size_t)(16 * tile + min(wave + NW * j, rows - 1)) * n_ssq;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sq[j][i] = sr[min(lane + 64 * i, n_ssq - 1)];
-    }
-#pragma unroll
-    for (int j = 0; j < RW; ++j) {
-        sum[j] = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sum[j] += lane + 64 * i < n_ssq ? sq[j][i] : 0.f;
-        if (n_ssq > 256) {
-            const float* sr = ssq + (size_t)(16 * tile + min(wave + NW * j, rows - 1)) * n_ssq;
-            for (int col = lane + 256; col < n_ssq; col += 64) sum[j] += sr[col];
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < RW; ++j) {
-        sum[j] = wave_sum(sum[j]);
-        if (lane == 0) s_inv[wave + NW * j] = 1.0f / sqrtf(sum[j] / (float)K + eps);
-    }
-    __syncthreads();
-    if (!mine) return;
-    const float inv = s_inv[e % rows];
+__global__ void __launch_bounds__(64) rms_rows_kernel(const float* xg, int ld, const float* ssq, int n_ssq, int K, float eps,
+                                                      int M, T* h) {
+    const int m = blockIdx.y, lane = threadIdx.x, k = 8 * ((int)blockIdx.x * 64 + lane);
+    const size_t off = frag_off(m, min(k, K - 8), ld, M);   // clamped into the row
+    const Frag<float> v = Frag<float>::load(xg + off);
+    const float* sr = ssq + (size_t)m * n_ssq;
+    float sum = 0.f;
+    for (int col = lane; col < n_ssq; col += 64) sum += sr[col];
+    const float inv = 1.0f / sqrtf(wave_sum(sum) / (float)K + eps);
     const float x[8] = {v.lo.x * inv, v.lo.y * inv, v.lo.z * inv, v.lo.w * inv,
                         v.hi.x * inv, v.hi.y * inv, v.hi.z * inv, v.hi.w * inv};
-    Frag<T>::from_f32(x).store(h + off);
+    if (k < K) Frag<T>::from_f32(x).store(h + off);
 }
 
 // One row of a large block (more than 64 rows), or of a decode block behind a
@@ -191,13 +162,13 @@ __global__ void __launch_bounds__(kNormRowMaxThreads) norm_rows_kernel(NormRowAr
 hipError_t launch_rms_rows(int dtype, const float* xg, int ld, const float* ssq, int n_ssq, int K, float eps, int M,
                            void* h, hipStream_t s) {
     if (M < 1) return hipSuccess;
-    if (K % 8 || ld < K) return hipErrorInvalidValue;   // whole chunks
-    const dim3 grid((unsigned)((std::min(M, 16) * (K / 8) + kRmsThreads - 1) / kRmsThreads), (unsigned)((M + 15) / 16));
+    if (K < 8 || K % 8 || ld < K) return hipErrorInvalidValue;   // whole chunks
+    const dim3 grid((unsigned)((K / 8 + 63) / 64), (unsigned)M);
     if (dtype == 1)
-        hipLaunchKernelGGL(rms_rows_kernel<uint16_t>, grid, dim3(kRmsThreads), 0, s, xg, ld, ssq, n_ssq, K, eps, M,
+        hipLaunchKernelGGL(rms_rows_kernel<uint16_t>, grid, dim3(64), 0, s, xg, ld, ssq, n_ssq, K, eps, M,
                            static_cast<uint16_t*>(h));
     else
-        hipLaunchKernelGGL(rms_rows_kernel<float>, grid, dim3(kRmsThreads), 0, s, xg, ld, ssq, n_ssq, K, eps, M,
+        hipLaunchKernelGGL(rms_rows_kernel<float>, grid, dim3(64), 0, s, xg, ld, ssq, n_ssq, K, eps, M,
                            static_cast<float*>(h));
     return hipGetLastError();
 }
