@@ -744,8 +744,8 @@ __device__ __forceinline__ int finish_row(const uint32_t (&keys)[N], const doubl
 // fetched once per launch and took most of its 66 us.  4 x 6 rows of 32016 ids: 66.5 -> 42.9 us.
 // Flat rows leave more than kNT kFew ids (std 1.3, T 0.8, p 0.95: 29000 of 32016; their nucleus alone is 16000)
 // and go to sample_row.  That is seen before the float64 exponentials are paid for: the ids above the first cut
-// are counted and placed first, and where that is more than one per thread a float32 sum says whether the cut
-// will hold.  The row waits in s_hist for sample_row, whose own load, 128 bytes apart per lane, costs more than
+// are counted and placed first, and where that is more than two per thread a float32 sum says whether the cut
+// will hold (2.7 us, which rows of fewer ids seldom need).  The row waits in s_hist for sample_row, whose own load, 128 bytes apart per lane, costs more than
 // this one.  4 x 6 rows of std 1.3 / 2 / 3 / 4: 67.2 / 70.5 / 48.6 / 42.9 us (with the exponentials before the
 // count 89.1 / 88.5 / 45.9 / 42.8, by sample_row alone 68.7 / 68.3 / 68.2 / 66.5).
 // First cut: near the highest that holds for normal logits of a standard deviation of 2 to 5 T.  Beyond p 0.95 the
@@ -814,7 +814,7 @@ __device__ __forceinline__ bool sample_row_few(const float* row, int V, double T
     float fl = f1;
     int total = places(f1);
     bool few = total <= kNT * kFew;
-    if (few && total > kNT) {   // will the first cut hold?  A float32 sum, which decides nothing but the route
+    if (few && total > 2 * kNT) {   // will the first cut hold?  A float32 sum, which decides nothing but the route
         const float c1 = (float)(r * 1.4426950408889634), c0 = (float)(zmax * 1.4426950408889634);
         float f[2] = {0.f, 0.f};
 #pragma unroll

@@ -42,14 +42,14 @@ def test_few(vocab, temp, p):
 
 
 # p; ids at each logit (the rest at -20) at T = 1, V = 32016.  First cut -9.0 (p 0.95) or -13.0 (p 0.99), second
-# -14.4 or -16.0; 8192 ids fit; beyond 1024 above the first cut the float32 sum decides.
+# -14.4 or -16.0; 8192 ids fit; beyond 2048 above the first cut the float32 sum decides.
 ROUTES = {
     "fits exactly": (0.95, {0.0: 1, -5.0: 8191, -9.2: 20000}),
     "one too many": (0.95, {0.0: 1, -5.0: 8192, -9.2: 20000}),
     "tail too heavy, second cut too many": (0.95, {0.0: 1, -5.0: 3000, -9.2: 29015}),
     "tail too heavy, seen after the sums": (0.95, {0.0: 1, -5.0: 1000, -9.2: 31015}),
     "second cut, few above the first": (0.95, {0.0: 1, -6.0: 20, -9.2: 5000}),
-    "second cut, many above the first": (0.95, {0.0: 1, -8.5: 1500, -9.2: 6600}),
+    "second cut, many above the first": (0.95, {0.0: 1, -8.5: 2100, -9.2: 6000}),
     "second cut fits exactly": (0.95, {0.0: 1, -6.0: 20, -9.2: 8171}),
     "p 0.99": (0.99, {0.0: 1, -8.0: 300, -12.9: 6000, -13.2: 20000}),
     "p 0.99, second cut": (0.99, {0.0: 1, -13.2: 8000}),
