@@ -70,8 +70,9 @@ typedef struct sdsat_config {
     int32_t max_block;   /* largest q (rows per sequence per block), <= 4096; also the
                             prefill block of sdsat_generate.  Blocks of more than 64 rows
                             in total (batch * q) run their linear layers as matrix-core
-                            GEMMs (fp32: on the caller's weights; d_ffn must then be a
-                            multiple of 8) and take no ancestor mask; decode blocks need
+                            GEMMs (fp32: on the caller's weights) and take no ancestor
+                            mask; where max_batch * max_block allows such blocks, d_ffn
+                            must be a multiple of 8.  Decode blocks need
                             batch * (k + 1) <= 64 */
 } sdsat_config;
 

@@ -159,6 +159,18 @@ hipError_t launch_stream_read(const void* src, size_t bytes, hipStream_t s);
 // rotary table [S][half][2]: cos and sin of the angle pos * inv_freq[i], formed in double, rounded to float
 hipError_t launch_rope_table(const double* inv_freq, int S, int half, float* rope, hipStream_t s);
 
+// ---------------------------------------------------------------- row kernels of decode blocks
+// The normalised rows of a decode block, rounded once for the GEMM that reads them:
+// h = elem(xg / rms) with rms from the row's per-16-column sums of squares; xg and h in fragment order
+// (M rows of ld columns; K a multiple of 8)
+hipError_t launch_rms_rows(int dtype, const float* xg, int ld, const float* ssq, int n_ssq, int K, float eps, int M,
+                           void* h, hipStream_t s);
+// The row kernel behind a split residual GEMM of a decode block (up to kFoldMaxParts partials, row stride and
+// part stride as the GEMM writes them): launch_resid_norm_rows for the fragment order of M rows
+constexpr int kFoldMaxParts = 8;
+hipError_t launch_fold_norm_rows(int dtype, const float* part, int parts, int M, int N, float* x, const float* g, float eps,
+                                 void* h, int ldh, hipStream_t s, hipEvent_t ev1 = nullptr);
+
 // ---------------------------------------------------------------- large blocks (prefill)
 // C[M][ldc] (float) = A[M][lda] (element type) . W[N][K]^T on the matrix cores, W = up to three
 // row-major [n_per, K] matrices stacked along N (W0 rows 0..n_per-1, W1 the next n_per, ...).
@@ -196,20 +208,11 @@ int prefill_mma_configs();
 hipError_t launch_prefill_mma(int cfg, const PrefillGemmArgs& p, hipStream_t s);
 hipError_t launch_prefill_gemm(int dtype, const PrefillGemmArgs& p, hipStream_t s);
 // Row-wise steps around the prefill GEMMs of blocks of more than 64 rows.
-// h = elem(xg / rms) with rms from the row's per-16-column sums of squares; xg and h in fragment order
-// (M rows of ld columns; K a multiple of 8)
-hipError_t launch_rms_rows(int dtype, const float* xg, int ld, const float* ssq, int n_ssq, int K, float eps, int M,
-                           void* h, hipStream_t s);
 // x += y with y = ((y_0 + y_1) + y_2) + ..., the parts of a split contraction (parts >= 1, part p at
 // y + p * part_stride); h = elem((x o g) / rms(x)), bitwise what the residual epilogue's per-16-column
 // sums of squares and rms_rows give (rows of up to 8192 columns).  h: fragment order, M rounded up to 16 rows
 hipError_t launch_resid_norm_rows(int dtype, const float* y, int parts, size_t part_stride, int ldy, int M, int N,
                                   float* x, int ldx, const float* g, float eps, void* h, int ldh, hipStream_t s);
-// The row kernel behind a split residual GEMM of a decode block (up to kFoldMaxParts partials, row stride and
-// part stride as the GEMM writes them): the same for h in the fragment order of M rows
-constexpr int kFoldMaxParts = 8;
-hipError_t launch_fold_norm_rows(int dtype, const float* part, int parts, int M, int N, float* x, const float* g, float eps,
-                                 void* h, int ldh, hipStream_t s, hipEvent_t ev1 = nullptr);
 // the same for layer 0: x = E[token] (ids out of range set *err bit 1 and read row 0)
 hipError_t launch_embed_norm_rows(int dtype, const void* embed, int n_rows_emb, const int* tokens, int M, int N, float* x,
                                   const float* g, float eps, void* h, int ldh, int* err, hipStream_t s);
